@@ -342,6 +342,12 @@ __device__ __forceinline__ void lds_store_u32x4(uint32_t addr, u32x4 v) {
 __device__ __forceinline__ void lds_store_u16(uint32_t addr, uint16_t v) {
   *(__attribute__((address_space(3))) uint16_t*)(size_t)addr = v;
 }
+__device__ __forceinline__ uint32_t lds_u32(uint32_t addr) {
+  return *(const __attribute__((address_space(3))) uint32_t*)(size_t)addr;
+}
+__device__ __forceinline__ void lds_store_u32(uint32_t addr, uint32_t v) {
+  *(__attribute__((address_space(3))) uint32_t*)(size_t)addr = v;
+}
 __device__ __forceinline__ int lds_u16(uint32_t addr) {
   return *(const __attribute__((address_space(3))) uint16_t*)(size_t)addr;
 }
@@ -1728,55 +1734,168 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
   }
 }
 
-// w_hat = s*q written densely (checking aid, not a hot path): four waves per
-// tile, each indexing slice `wave` of every unit (one window) and writing its
-// entries, one lane per entry.
-constexpr int kDequantWaves = 4;
+// ---------------------------------------------------------------------------
+// Entries looked up from the width map in registers (no index in LDS).
+//
+// Lane l of a wave holds width-map word w0 + l of a unit and the class counts
+// of the words before it (a prefix sum over the lanes).  For word w the wave
+// reads both planes and the four counts back as scalars, and lane l then stands
+// for position 64w + l: its rank inside its class is a masked bit count of the
+// class mask, started at the word's first entry, and three selects pick its
+// class's address.
+// ---------------------------------------------------------------------------
+struct WordScan {
+  uint64_t p0, p1;      // planes of word w0 + lane
+  uint32_t ex01, ex23;  // class counts of words w0 .. w0 + lane - 1 (16-bit halves)
+  uint32_t t01, t23;    // of all 64 words (wave-uniform)
+};
 
-__global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatrix mat, float* W, int region_bytes) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+// Inclusive prefix sum over the wave: inside each row of 16 lanes, then the
+// rows' totals (row broadcasts).
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
+  v += dpp<kDppShr1>(v);
+  v += dpp<kDppShr2>(v);
+  v += dpp<kDppShr4>(v);
+  v += dpp<kDppShr8>(v);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // lane 15 of rows 0, 2 to rows 1, 3
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // lane 31 to rows 2, 3
+  return v;
+}
+
+// Words w0 .. w0 + 63 of the unit (words past its last one count nothing).
+__device__ __forceinline__ WordScan scan_words(const DevMatrix& mat, const UnitInfo& u, int w0, uint32_t lane) {
+  const uint32_t last = mat.wmap_words - 1;
+  const int w = w0 + (int)lane;
+  const uint32_t wc = (uint32_t)min(w, u.W - 1);
+  WordScan r;
+  r.p0 = ld<uint64_t>(mat.blob, mat.off_wmap + 8u * min(u.wmap_word + wc, last));
+  r.p1 = ld<uint64_t>(mat.blob, mat.off_wmap + 8u * min(u.wmap_word + (uint32_t)u.W + wc, last));
+  uint64_t m[4];
+  class_masks(r.p0, r.p1, valid_mask(w, u.npos, mat.R, u.rows), m);
+  // 16-bit halves: a unit has at most 8192 positions
+  const uint32_t c01 = (uint32_t)__popcll(m[0]) | ((uint32_t)__popcll(m[1]) << 16);
+  const uint32_t c23 = (uint32_t)__popcll(m[2]) | ((uint32_t)__popcll(m[3]) << 16);
+  const uint32_t i01 = wave_prefix(c01), i23 = wave_prefix(c23);
+  r.ex01 = i01 - c01;
+  r.ex23 = i23 - c23;
+  r.t01 = __builtin_amdgcn_readlane(i01, 63);
+  r.t23 = __builtin_amdgcn_readlane(i23, 63);
+  return r;
+}
+
+// The entry at each lane's position of word w0 + l of a scan: byte offset of
+// its codes with the class in the low three bits (code sections and entries
+// are 8-byte aligned), byte offset of its scale, and whether the position is
+// real.  start: the class runs' entries at word w0.  Entries are clamped into
+// their section (a malformed blob can make the map and the unit table disagree).
+struct LaneEntry {
+  uint32_t codes, scale;
+  bool real;
+};
+
+__device__ __forceinline__ LaneEntry word_entries(const DevMatrix& mat, const UnitInfo& u, const WordScan& sc,
+                                                  const uint32_t start[4], int w0, int l) {
+  const uint64_t p0 = read_lane64(sc.p0, l), p1 = read_lane64(sc.p1, l);
+  const uint32_t e01 = __builtin_amdgcn_readlane(sc.ex01, l), e23 = __builtin_amdgcn_readlane(sc.ex23, l);
+  const uint32_t ex[4] = {e01 & 0xFFFFu, e01 >> 16, e23 & 0xFFFFu, e23 >> 16};
+  const uint64_t valid = valid_mask(w0 + l, u.npos, mat.R, u.rows);
+  uint64_t m[4];
+  class_masks(p0, p1, valid, m);
+  uint32_t codes[4], scale[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    uint32_t g = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[c] >> 32),
+                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m[c], start[c] + ex[c]));
+    g = min(g, max(mat.n_entries[c], 1u) - 1u);
+    codes[c] = (mat.off_codes[c] | (uint32_t)c) + (g << (3 + c));
+    scale[c] = mat.off_scales[c] + 2u * g;
+  }
+  LaneEntry e;
+  e.codes = codes[0];
+  e.scale = scale[0];
+#pragma unroll
+  for (int c = 1; c < 4; ++c) {
+    e.codes = __builtin_amdgcn_inverse_ballot_w64(m[c]) ? codes[c] : e.codes;
+    e.scale = __builtin_amdgcn_inverse_ballot_w64(m[c]) ? scale[c] : e.scale;
+  }
+  e.real = __builtin_amdgcn_inverse_ballot_w64(valid);
+  return e;
+}
+
+// w_hat = s*q written densely.  Bound by the stores (256 bytes a group).  A
+// wave takes the words of one slice of a unit: the word's 64 entries are
+// looked up a lane each and handed to groups of 16 lanes through LDS (64
+// words), so each lane expands the four weights 4t .. 4t + 3 of an entry from
+// one dword of codes and the wave stores four whole groups per instruction,
+// 16 bytes a lane.  For 16-row tiles a word is 16 rows of four columns and the
+// four groups of a store are consecutive in memory.
+constexpr int kDequantWaves = 4;
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // W may be only 4-byte aligned
+
+__global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatrix mat, float* W, int S) {
+  __shared__ __attribute__((aligned(16))) uint32_t hand_s[kDequantWaves * 128];  // per position: codes and class, scale
   const uint32_t lane = lane_id();
   const int wave = wave_id();
   const int t = blockIdx.x;
-  const int R = mat.R;
-  const uint32_t inv = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)smem + (uint32_t)(wave * region_bytes);
-  for (int k = 0; k < mat.U; ++k) {
+  const uint32_t hand = (uint32_t)(size_t)(__attribute__((address_space(3))) uint32_t*)hand_s + 512u * (uint32_t)wave;
+  const uint32_t grp = lane >> 4, sub = lane & 15u;
+  const uint32_t mine = hand + 128u * grp;
+  for (int item = wave; item < mat.U * S; item += kDequantWaves) {
+    const int k = item / S, sl = item - k * S;
     const UnitInfo u = load_unit(mat, t, k);
+    const int per = (u.W + S - 1) / S;
+    const int wb = min(u.W, sl * per), we = min(u.W, wb + per);
+    if (wb >= we) continue;
     const int unit = t * mat.U + k;
-    int cb, ce;
-    slice_cols(u.cols, R, wave, kDequantWaves, cb, ce);
-    if (cb >= ce) continue;
-    const int wb = (cb * R) >> 6, we = (ce * R + 63) >> 6;
-    const WmapRegs wr = load_wmap(mat, u, we, lane);
-    const WinCounts wc = window_counts(wr, u, wb, we, R, lane);
-    build_index(wr, u, wb, we, R, wc, inv, lane);
-    lds_phase();
-    uint32_t seg = inv;
-    for (int c = 0; c < 4; ++c) {
-      const int B = 1 << c, NWc = 2 * B, per = 16 / B;
-      const uint32_t mask = (1u << B) - 1;
-      const uint32_t start = class_start(mat, unit, c) + wc.before[c];
-      const int n = clamp_run(mat, c, start, wc.own[c]);
-      for (int e = (int)lane; e < n; e += 64) {
-        const int p = lds_u16(seg + 2u * (uint32_t)e) + wb * 64;  // unit position
-        const int jl = p >> mat.logR, r = p & (R - 1);
-        const size_t g = (size_t)start + e;
-        const uint32_t* wv = (const uint32_t*)(mat.blob + mat.off_codes[c]) + g * NWc;
-        const float s = (float)__builtin_bit_cast(_Float16, ld<uint16_t>(mat.blob, mat.off_scales[c] + 2u * (uint32_t)g));
-        float* dst = W + ((size_t)t * R + r) * mat.K + (size_t)(u.j0 + jl) * 64;
-        for (int i = 0; i < 32; ++i) {
-          const uint32_t word = wv[i / per];
-          const int f = i % per;
-          const int u0 = (int)((word >> (f * B)) & mask), u1 = (int)((word >> (16 + f * B)) & mask);
-          const int q0 = c == 0 ? 2 * u0 - 1 : u0 - (1 << (B - 1));
-          const int q1 = c == 0 ? 2 * u1 - 1 : u1 - (1 << (B - 1));
-          dst[2 * i] = s * (float)q0;
-          dst[2 * i + 1] = s * (float)q1;
+    uint32_t start[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) start[c] = class_start(mat, unit, c);
+    for (int w0 = 0; w0 < we; w0 += 64) {
+      const WordScan sc = scan_words(mat, u, w0, lane);
+      for (int w = max(wb, w0); w < min(we, w0 + 64); ++w) {
+        const LaneEntry e = word_entries(mat, u, sc, start, w0, w - w0);
+        lds_store_u32(hand + 8u * lane, e.codes);
+        const uint32_t sbits = ld<uint16_t>(mat.blob, e.scale);
+        // the 16 positions of this lane's group: consecutive rows of one column
+        const int p0 = w * 64 + 16 * (int)grp;
+        const int row0 = p0 & (mat.R - 1), col = p0 >> mat.logR;
+        const int n = col < u.cols ? min(16, u.rows - row0) : 0;
+        lds_phase();
+        uint32_t code[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const uint32_t a = lds_u32(mine + 8u * (uint32_t)i);
+          // weights 4 sub .. + 3 are pairs 2 sub, 2 sub + 1: one dword at every width
+          code[i] = ld<uint32_t>(mat.blob, (a & ~7u) + (((sub << (a & 3u)) >> 3) << 2));
+          __builtin_amdgcn_sched_barrier(0x7F0);  // address arithmetic stays with its load (register use)
         }
+        lds_phase();
+        lds_store_u32(hand + 8u * lane + 4u, __float_as_uint((float)__builtin_bit_cast(_Float16, (uint16_t)sbits)));
+        lds_phase();
+        float* dst = W + ((size_t)t * mat.R + row0) * mat.K + (size_t)(u.j0 + col) * 64 + 4u * sub;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const u32x2 h = *(const __attribute__((address_space(3))) u32x2*)(size_t)(mine + 8u * (uint32_t)i);
+          const uint32_t c = h.x & 3u, B = 1u << c, mask = (1u << B) - 1u;
+          const float s = __uint_as_float(h.y);
+          const uint32_t v = code[i] >> (((2u * sub) << c) & 15u);  // the pairs' bit offset in each half-word
+          const float mul = c == 0u ? 2.0f : 1.0f, off = c == 0u ? -1.0f : -(float)(1u << (B - 1u));
+          f32x4_a4 o;
+          o.x = s * __builtin_fmaf((float)(v & mask), mul, off);
+          o.y = s * __builtin_fmaf((float)((v >> 16) & mask), mul, off);
+          o.z = s * __builtin_fmaf((float)((v >> B) & mask), mul, off);
+          o.w = s * __builtin_fmaf((float)((v >> (16u + B)) & mask), mul, off);
+          if (i < n) __builtin_nontemporal_store(o, (f32x4_a4*)dst);
+          dst += mat.K;
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        lds_phase();
       }
-      seg += 2u * wc.own[c];
+      start[0] += sc.t01 & 0xFFFFu;
+      start[1] += sc.t01 >> 16;
+      start[2] += sc.t23 & 0xFFFFu;
+      start[3] += sc.t23 >> 16;
     }
-    lds_phase();
   }
 }
 
@@ -2608,12 +2727,14 @@ vbq_status vbq_dequant(const vbq_desc* desc, const void* blob_dev, float* W_dev,
   vbq_status st = make_dev_matrix(desc, blob_dev, &m);
   if (st != VBQ_OK) return st;
   if ((uintptr_t)W_dev % 4) return VBQ_ERR_BUFFER;
-  // one uint16 per position of the widest wave slice, rounded up to whole words
-  int region = align16(((max_slice_cols(m.R, m.C, kDequantWaves) * m.R + 63) / 64) * 64 * 2);
-  void* args[] = {&m, &W_dev, &region};
-  const int lds = kDequantWaves * region;
-  return hip_status(hipLaunchKernel((const void*)vbq_dequant_kernel, dim3((unsigned)m.T), dim3(kDequantWaves * 64), args,
-                                    (size_t)lds, (hipStream_t)stream));
+  // slices of a unit's words: enough waves for eight per SIMD (the rate comes
+  // from the stores and loads in flight), a word at least each
+  const int64_t units = (int64_t)m.T * m.U;
+  const int unit_words = (int)(((int64_t)m.C * m.R + 63) / 64);
+  int S = (int)std::min<int64_t>(std::max<int64_t>((8192 + units - 1) / units, (kDequantWaves + m.U - 1) / m.U), unit_words);
+  void* args[] = {&m, &W_dev, &S};
+  return hip_status(hipLaunchKernel((const void*)vbq_dequant_kernel, dim3((unsigned)m.T), dim3(kDequantWaves * 64), args, 0,
+                                    (hipStream_t)stream));
 }
 
 vbq_status vbq_step_plan_bytes(int32_t n, size_t* bytes) {
