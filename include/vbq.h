@@ -117,10 +117,11 @@ typedef enum vbq_status {
  *                         by vbq_dequant.
  *   VBQ_ONE_WAVE_PER_UNIT the one- and two-row products use one wave per unit
  *                         even where the library would use two (small
- *                         mixed-width matrices).  Results agree within the
- *                         output tolerance, bitwise where both take whole
- *                         units; it exists so both kernels can be compared on
- *                         the same inputs. */
+ *                         mixed-width matrices) or, for two rows, matrix cores
+ *                         (one width, or more than 2048 units).  Results agree
+ *                         within the output tolerance, bitwise between one and
+ *                         two waves where both take whole units; it exists so
+ *                         the kernels can be compared on the same inputs. */
 #define VBQ_Y_F16 1u
 #define VBQ_ONE_WAVE_PER_UNIT 2u
 #define VBQ_CALL_FLAGS (VBQ_Y_F16 | VBQ_ONE_WAVE_PER_UNIT)

@@ -1435,306 +1435,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(MT == 1
 }
 
 // ---------------------------------------------------------------------------
-// Several activation rows (3 <= M <= 16): matrix cores.
-//
-// Y[m][n] = sum_k w_hat[n][k] X[m][k] as 16 x 16 x 16 fp16 MFMA products
-// D[m][r] = sum_k X[m][k] q_r[k] over the 16 entries r of one group column
-// and 16 consecutive rows (a "block"), whatever their widths:
-//   * lane l works for weight row r = l % 16 and, over the four products kb,
-//     for group positions 16 (l/16) .. + 15 (product kb takes 16 (l/16) + 4 kb
-//     .. + 3: the k order inside a product is free as long as A and B agree);
-//   * A: activations X[l % 16][64 col + 16 (l/16) ..] (two 16-byte loads);
-//   * B: the levels q of row r's entry, made exactly in fp16: a code field ORed
-//     into the mantissa of 1024.0 reads as 1024 + u, and packed fp16 adds give
-//     q.  Each lane decodes its own entry's width with per-lane field
-//     positions, masks and offsets, so every lane runs the same code;
-//   * D: lane l holds D[4 (l/16) + j][l % 16], j = 0..3, so each lane adds
-//     s * D for its weight row and four activation rows to registers over the
-//     slice's columns, in column order (results are bitwise repeatable).
-// A position's entry comes from a per-slice map position -> (class, rank in
-// the slice's class run) built from the width map.
-// ---------------------------------------------------------------------------
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
-
-constexpr int kMmRows = 16;
-constexpr int kMmMaxCols = 32;  // group columns of a slice
-
-struct MmArgs {
-  DevMatrix m;
-  const uint16_t* x;  // fp16 bits, row m at x + m*ldx
-  void* y;            // row m at y + m*ldy elements (float, or fp16 bits when yf16)
-  int64_t ldx, ldy;
-  int32_t M;          // rows of X (3..16)
-  int32_t S;          // slices per unit
-  int32_t yf16;       // 1: y holds fp16
-};
-
-// Bytes of one wave's LDS region: row sums (16 x R floats), the per-class
-// table of the slice (five rows of eight words), and the position -> entry
-// map (uint16 per position of the widest slice).
-constexpr int kMmTableBytes = 5 * 32;
-__host__ __device__ inline int mm_wave_bytes(int R, int cols) {
-  return kMmRows * R * 4 + kMmTableBytes + align16(((cols * R + 63) / 64) * 64 * 2);
-}
-
-// The table a lane reads for its block's entry, row c of width class c (row
-// 4: class 0 for lanes with odd h, whose 1-bit fields sit 8 bits higher):
-//   word 0..3  code section offset, scale section offset, slice run start,
-//              last entry of the class section (addresses of the entry);
-//   word 4     field mask of one pair (two codes, one per half-word): 1 bit
-//              codes are read from the word rotated right by 31 (even h:
-//              fields 0..7 move up one bit) or by 7 (odd h: fields 8..15 move
-//              down seven), so a field shifted by its offset lands at bit 1 of
-//              each half, and no field crosses the word's ends;
-//   word 5     -(1024 + offset) in both fp16 halves: a masked field ORed into
-//              1024.0 reads as 1024 + u (1024 + 2u for 1 bit), and one
-//              packed add makes the level q exactly (1025 for 1 bit, 1024 +
-//              2^(b-1) otherwise: integers below 2048, exact in fp16);
-//   word 6     the field's bit offset (in the rotated word) for products
-//              kb = 0..3, one per byte;
-//   word 7     the pair's second field offset b | (3 + c) << 8 (log2 of the
-//              entry's bytes) | c << 16 | rotation << 24.
-// Row `row` of the table (lane 0 of the wave writes all five once per slice;
-// the values are wave-uniform): code and scale section offsets, the slice's
-// run start and the class section's last entry.
-template <int row>
-__device__ __forceinline__ void write_mm_row(uint32_t tab, uint32_t offc, uint32_t offs, uint32_t start,
-                                             uint32_t lim) {
-  constexpr uint32_t c = row == 4 ? 0u : (uint32_t)row;
-  constexpr uint32_t kMask[4] = {0x00020002u, 0x00030003u, 0x000F000Fu, 0x00FF00FFu};
-  constexpr uint32_t kSub[4] = {0xE401E401u, 0xE402E402u, 0xE408E408u, 0xE480E480u};
-  constexpr uint32_t kShift[4] = {0x06040200u, 0x0C080400u, 0x08000800u, 0u};
-  constexpr uint32_t rot = row == 4 ? 7u : row == 0 ? 31u : 0u;
-  lds_store_u32x4(tab + 32u * row, u32x4{offc, offs, start, lim});
-  lds_store_u32x4(tab + 32u * row + 16u,
-                  u32x4{kMask[c], kSub[c], kShift[c], (1u << c) | ((3u + c) << 8) | (c << 16) | (rot << 24)});
-}
-
-// One block in registers for this lane: its entry's 16 code bytes that hold
-// the lane's 16 levels, the class table's decoding words, the fp16 scale bits
-// (zero-extended), and 16 activations of row l % 16.  A lane of a padding row
-// (past the matrix's last row) decodes a clamped in-range entry: its product
-// column is that row's alone and is never added to a row sum, so no value
-// loaded for it needs a select (which would wait for the load).
-struct MmBlock {
-  u32x4 w;
-  u32x4 k;   // table words 4..7 of the entry's class
-  uint32_t s;
-  u32x4 a0, a1;
-};
-
-// Block f of the row group: column f / RB, row block rg*RB + f % RB.  The
-// lane's levels 16h .. 16h + 15 (h = lane / 16) are pairs 8h .. 8h + 7, whose
-// codes start at byte (2h << c) & ~3 of the entry.  Loads are unconditional
-// (clamped), so the next block stays in flight.  X comes through a buffer
-// resource (xr) covering the M rows.
-template <int RB>
-__device__ __forceinline__ void load_mm_block(MmBlock& bk, __amdgpu_buffer_rsrc_t xr, int64_t ldx, int M,
-                                              const DevMatrix& mat, uint32_t fwd, uint32_t tab, int f, int rg,
-                                              int rows, int j0, uint32_t lane) {
-  const int R = mat.R;
-  const uint32_t e = lane & 15u, h = lane >> 4;
-  const int col = f / RB;
-  const int row = (rg * RB + f % RB) * 16 + (int)e;
-  const uint32_t v = (uint32_t)lds_u16(fwd + 2u * (uint32_t)(col * R + row));
-  const bool real = row < rows;
-  const uint32_t c = real ? v >> 14 : 0u;
-  const uint32_t trow = (c == 0u && (h & 1u)) ? 4u : c;
-  const u32x4 t0 = lds_u32x4(tab + 32u * trow);
-  bk.k = lds_u32x4(tab + 32u * trow + 16u);
-  const uint32_t g = min(t0.z + (real ? (v & 0x3FFFu) : 0u), t0.w);
-  bk.w = ld<u32x4>(mat.blob, t0.x + (g << (3 + c)) + (((2u * h) << c) & ~3u));
-  bk.s = (uint32_t)ld<uint16_t>(mat.blob, t0.y + 2u * g);
-  const int m = min((int)e, M - 1);
-  const uint32_t xo = 2u * (uint32_t)((int64_t)m * ldx + (int64_t)(j0 + col) * 64 + 16 * (int)h);
-  bk.a0 = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)xo, 0, 0);
-  bk.a1 = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)xo + 16, 0, 0);
-}
-
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-
-// s * D of one block, two 16 x 16 x 32 products (weights 16h .. 16h + 7 and
-// 16h + 8 .. 16h + 15 of the lane's entry against the same activations).
-// For kb = 0..3 the lane's pairs 8h + 2kb, + 1 are fields f, f + 1 of word
-// wi of its 16 code bytes:
-//   1 bit: wi = 0, f = 8 (h & 1) + 2kb;  2 bits: wi = 0, f = 2kb;
-//   4 bits: wi = kb / 2, f = 2 (kb & 1); 8 bits: wi = kb, f = 0.
-__device__ __forceinline__ float4_t mm_products(const MmBlock& bk) {
-  const uint32_t c = (bk.k.w >> 16) & 0xFFu, B = bk.k.w & 0xFFu;
-  const uint32_t mask = bk.k.x, sub = bk.k.y, shifts = bk.k.z;
-  const uint32_t src0 = __builtin_amdgcn_alignbit(bk.w.x, bk.w.x, bk.k.w >> 24);
-  const uint32_t src1 = c == 3u ? bk.w.y : src0;
-  const uint32_t src2 = c == 3u ? bk.w.z : c == 2u ? bk.w.y : src0;
-  const uint32_t src3 = c == 3u ? bk.w.w : c == 2u ? bk.w.y : src0;
-  const uint32_t word[4] = {src0, src1, src2, src3};
-  uint32_t q[8];
-#pragma unroll
-  for (int kb = 0; kb < 4; ++kb) {
-    const uint32_t sh = (shifts >> (8 * kb)) & 0xFFu;
-    const uint32_t v0 = ((word[kb] >> sh) & mask) | 0x64006400u;  // 1024 + u (1024 + 2u for 1 bit)
-    const uint32_t v1 = ((word[kb] >> (sh + B)) & mask) | 0x64006400u;
-    q[2 * kb] = __builtin_bit_cast(uint32_t, as_h2(v0) + as_h2(sub));
-    q[2 * kb + 1] = __builtin_bit_cast(uint32_t, as_h2(v1) + as_h2(sub));
-  }
-  const half8_t b0 = __builtin_bit_cast(half8_t, u32x4{q[0], q[1], q[2], q[3]});
-  const half8_t b1 = __builtin_bit_cast(half8_t, u32x4{q[4], q[5], q[6], q[7]});
-  float4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
-  d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, bk.a0), b0, d, 0, 0, 0);
-  d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, bk.a1), b1, d, 0, 0, 0);
-  const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)bk.s);
-  return d * s;
-}
-
-// Marks a block's registers as read here: every buffer's load is consumed on
-// every path, so no register with a load in flight is ever reused for
-// something else (which would make the compiler wait for all loads).
-__device__ __forceinline__ void mm_done(const MmBlock& bk) {
-  __asm__ __volatile__("" ::"v"(bk.w), "v"(bk.s), "v"(bk.a0), "v"(bk.a1), "v"(bk.k));
-}
-
-// As for the one-row kernel, the values the first loads depend on come as
-// preloaded leading arguments (geo packs R, C, log2 R and S the same way),
-// the unit table is read beside the width map rather than after it, and the
-// argument block is read only once those loads are issued.
-template <int NW, int RB>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void vbq_mm_kernel(const uint8_t* __restrict__ blob, uint32_t off_wmap,
-                                                         uint32_t tile_words, uint32_t chunk_words, uint32_t wmap_words,
-                                                         int32_t G, int32_t N, uint32_t geo, int32_t U, MmArgs a) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  DevMatrix mat = a.m;
-  mat.blob = blob;
-  mat.off_wmap = off_wmap;
-  mat.tile_words = tile_words;
-  mat.chunk_words = chunk_words;
-  mat.wmap_words = wmap_words;
-  mat.G = G;
-  mat.N = N;
-  mat.U = U;
-  mat.R = (int)(geo & 0x1FF);
-  mat.C = (int)((geo >> 9) & 0xFF);
-  mat.logR = (int)((geo >> 17) & 0xF);
-  const int R = mat.R, S = (int)((geo >> 21) & 0x3FF);
-  const bool setup_prio = (geo >> 31) != 0u;  // raised issue priority for each item's set-up
-  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)smem;
-  const int wave = wave_id();
-  const int t = blockIdx.x;  // one row tile per workgroup
-  const int cmax = max_slice_cols(R, mat.C, S);
-  const int wbytes = mm_wave_bytes(R, cmax);
-  const uint32_t ysum = lds0 + (uint32_t)(wave * wbytes);
-  const uint32_t tab = ysum + (uint32_t)(kMmRows * R * 4);
-  const uint32_t fwd = tab + (uint32_t)kMmTableBytes;
-  const int rows = min(R, mat.N - t * R);
-  {
-    const uint32_t lane = lane_id_here();
-    for (int i = (int)lane; i < kMmRows * R; i += 64) lds_store_f32(ysum + 4u * i, 0.0f);
-  }
-  for (int item = wave; item < mat.U * S; item += NW) {
-    const uint32_t lane = lane_id_here();
-    const uint32_t h = lane >> 4;
-    const int k = item / S, sl = item - k * S;
-    const UnitInfo u = load_unit(mat, t, k);
-    const int unit = t * mat.U + k;
-    int cb, ce;
-    slice_cols(u.cols, R, sl, S, cb, ce);
-    if (cb >= ce) continue;  // wave-uniform: an empty slice
-    if (setup_prio) __builtin_amdgcn_s_setprio(1);
-    const int wb = (cb * R) >> 6, we = (ce * R + 63) >> 6;
-    const WmapRegs wr = load_wmap(mat, u, we, lane);
-    const u32x16 rows2 = unit_rows_vec(mat, unit);  // beside the width map, not after it
-    const uint32_t es[4] = {rows2.s0, rows2.s1, rows2.s2, rows2.s3};
-    // values from the kernel-argument block only after the loads above are
-    // issued (the compiler would otherwise hoist them and wait for the block)
-    lds_phase();
-    const uint16_t* xp = (const uint16_t*)opaque64((uint64_t)a.x);
-    const int64_t ldx = (int64_t)opaque64((uint64_t)a.ldx);
-    const int M = (int)opaque((uint32_t)a.M);
-    // X rows 0 .. M-1 (fp16, stride ldx): the bytes up to the end of row M-1
-    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)xp, 0, (int)(2 * ((int64_t)(M - 1) * ldx + mat.K)), 0x00020000);
-    const WinCounts wc = window_counts(wr, u, wb, we, R, lane);
-#define VBQ_MM_ROW(row, c)                                                                          \
-  write_mm_row<row>(tab, opaque(mat.off_codes[c]), opaque(mat.off_scales[c]),                       \
-                    uniform((int)(es[c] + wc.before[c])), uniform((int)(max(opaque(mat.n_entries[c]), 1u) - 1u)))
-    if (lane == 0) {
-      VBQ_MM_ROW(0, 0);
-      VBQ_MM_ROW(1, 1);
-      VBQ_MM_ROW(2, 2);
-      VBQ_MM_ROW(3, 3);
-      VBQ_MM_ROW(4, 0);
-    }
-#undef VBQ_MM_ROW
-    build_index<true>(wr, u, wb, we, R, wc, fwd, lane);
-    lds_phase();
-    if (setup_prio) __builtin_amdgcn_s_setprio(0);
-    const int j0 = u.j0 + cb;
-    const int nf = (ce - cb) * RB;  // blocks per row group
-    const int last = nf - 1;
-    for (int rg = 0; rg < R / (16 * RB); ++rg) {
-      float4_t acc[RB];
-#pragma unroll
-      for (int i = 0; i < RB; ++i) acc[i] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-      // Two blocks in flight (the next one loads while one is multiplied):
-      // with four, every wave's chain of index lookups and loads got longer
-      // (1.46B-class step at M = 4: 1415 against 1262 us).  With more than
-      // four rows of X, tiles of one or four row blocks take one block at a
-      // time (their blocks read more X; at M = 16 the step took 1551 against
-      // 1603 us, at M = 4 it would take 1281 against 1264).  Block f adds
-      // into acc[f % RB] (the ring slot) either way.
-      MmBlock B0, B1;
-      if (RB != 2 && M > 4) {  // wave-uniform
-        for (int f = 0; f < nf; ++f) {
-          load_mm_block<RB>(B0, xr, ldx, M, mat, fwd, tab, f, rg, rows, j0, lane);
-          acc[f % RB] += mm_products(B0);
-          mm_done(B0);
-        }
-      } else {
-      load_mm_block<RB>(B0, xr, ldx, M, mat, fwd, tab, 0, rg, rows, j0, lane);
-      for (int f = 0; f < nf; f += 4) {
-        load_mm_block<RB>(B1, xr, ldx, M, mat, fwd, tab, min(f + 1, last), rg, rows, j0, lane);
-        acc[0 % RB] += mm_products(B0);
-        mm_done(B0);
-        load_mm_block<RB>(B0, xr, ldx, M, mat, fwd, tab, min(f + 2, last), rg, rows, j0, lane);
-        if (f + 1 < nf) acc[1 % RB] += mm_products(B1);
-        mm_done(B1);
-        load_mm_block<RB>(B1, xr, ldx, M, mat, fwd, tab, min(f + 3, last), rg, rows, j0, lane);
-        if (f + 2 < nf) acc[2 % RB] += mm_products(B0);
-        mm_done(B0);
-        load_mm_block<RB>(B0, xr, ldx, M, mat, fwd, tab, min(f + 4, last), rg, rows, j0, lane);
-        if (f + 3 < nf) acc[3 % RB] += mm_products(B1);
-        mm_done(B1);
-      }
-      mm_done(B0);
-      }
-      // this wave's share of the row sums (several items add up in order)
-#pragma unroll
-      for (int i = 0; i < RB; ++i) {
-        const int row = (rg * RB + i) * 16 + (int)(lane & 15u);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int m = 4 * (int)h + j;
-          if (m < M && row < rows) {
-            const uint32_t ya = ysum + 4u * (uint32_t)(m * R + row);
-            lds_store_f32(ya, lds_f32(ya) + acc[i][j]);
-          }
-        }
-      }
-    }
-    lds_phase();
-  }
-  __syncthreads();
-  for (int slot = threadIdx.x; slot < kMmRows * R; slot += NW * 64) {
-    const int m = slot / R, r = slot - m * R;
-    if (m < a.M && r < rows) {
-      float tot = 0.0f;
-#pragma unroll
-      for (int w2 = 0; w2 < NW; ++w2) tot += lds_f32(lds0 + (uint32_t)(w2 * wbytes) + 4u * (uint32_t)slot);
-      store_y(a.y, m * a.ldy + (size_t)t * R + r, tot, a.yf16);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Entries looked up from the width map in registers (no index in LDS).
 //
 // Lane l of a wave holds width-map word w0 + l of a unit and the class counts
@@ -1798,7 +1498,8 @@ __device__ __forceinline__ LaneEntry word_entries(const DevMatrix& mat, const Un
   const uint64_t p0 = read_lane64(sc.p0, l), p1 = read_lane64(sc.p1, l);
   const uint32_t e01 = __builtin_amdgcn_readlane(sc.ex01, l), e23 = __builtin_amdgcn_readlane(sc.ex23, l);
   const uint32_t ex[4] = {e01 & 0xFFFFu, e01 >> 16, e23 & 0xFFFFu, e23 >> 16};
-  const uint64_t valid = valid_mask(w0 + l, u.npos, mat.R, u.rows);
+  uint64_t valid = ~0ull;
+  if (u.rows != mat.R || (w0 + l) * 64 + 64 > u.npos) valid = valid_mask(w0 + l, u.npos, mat.R, u.rows);  // wave-uniform
   uint64_t m[4];
   class_masks(p0, p1, valid, m);
   uint32_t codes[4], scale[4];
@@ -1820,6 +1521,416 @@ __device__ __forceinline__ LaneEntry word_entries(const DevMatrix& mat, const Un
   }
   e.real = __builtin_amdgcn_inverse_ballot_w64(valid);
   return e;
+}
+
+// ---------------------------------------------------------------------------
+// Several activation rows (M <= 16): matrix cores.
+//
+// Y[m][n] = sum_k w_hat[n][k] X[m][k] as 16 x 16 x 32 fp16 MFMA products
+// D[m][r] = sum_k X[m][k] q_r[k] over the 16 entries r of one group column
+// and 16 consecutive rows (a "block"), whatever their widths:
+//   * lane l works for weight row r = l % 16 and group positions 16h .. 16h + 15,
+//     h = l / 16 (the k order inside a product is free as long as A and B agree);
+//   * A: activations X[l % 16][64 col + 16h ..] (two 16-byte loads);
+//   * B: the levels q of row r's entry, made exactly in fp16: a code field ORed
+//     into the mantissa of 1024.0 reads as 1024 + u, and one packed fp16 add
+//     gives q.  Each lane decodes its own entry's width with per-lane field
+//     positions, masks and offsets, so every lane runs the same code;
+//   * D: lane l holds D[4h + j][l % 16], j = 0..3, so each lane adds s * D for
+//     its weight row and four activation rows to registers over the slice's
+//     columns, in column order (results are bitwise repeatable).
+// A wave takes a width-map word at a time, 64 positions = four blocks: 16 rows
+// of four columns (R = 16), 32 of two, or 64 rows of one.  Each lane looks up
+// one position's entry in registers and the four rows of 16 lanes are then
+// broadcast over the wave (lane-row swaps), so nothing of the lookup goes
+// through LDS and the loads of a whole word go out together, one word ahead of
+// the products.
+//
+// What bounds it: instruction issue (large matrices: about 330 instructions a
+// word, 240 of them VALU), two dependent memory trips (small ones), and for
+// 16-row tiles the reads of X, 2 KB a column for every tile.  Measured against
+// the earlier kernel (position map in LDS, then one block's lookup, loads and
+// products at a time), us a launch from a graph: 50304 x 2048 mixed M = 4 / 16
+// 29.3 / 43.5 -> 17.9 / 20.0, 16384 x 2048 M = 16 15.2 -> 9.4, 2048 x 8192
+// M = 16 13.2 -> 11.4, 2048 x 2048 M = 4 6.7 -> 4.2; one width, 28672 x 4096
+// 1-bit M = 8 30.3 -> 13.6, 2048 x 8192 2-bit M = 8 10.0 -> 8.5.  Two words
+// ahead were slower (25.0 at M = 16 on the 50304-row matrix) and no word ahead
+// with more waves equal at best (21.0).
+// ---------------------------------------------------------------------------
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kMmMaxCols = 32;  // group columns of a slice
+
+struct MmArgs {
+  DevMatrix m;
+  const uint16_t* x;  // fp16 bits, row m at x + m*ldx
+  void* y;            // row m at y + m*ldy elements (float, or fp16 bits when yf16)
+  int64_t ldx, ldy;
+  int32_t M;          // rows of X (1..16)
+  int32_t S;          // slices per unit
+  int32_t yf16;       // 1: y holds fp16
+};
+
+// Bytes of one wave's LDS region: decoding constants and the row sums of the M
+// rows of X (rounded up to the four that a lane holds).
+constexpr int kMmTableBytes = 16 * 32;
+__host__ __device__ inline int mm_wave_bytes(int R, int M) { return kMmTableBytes + ((M + 3) & ~3) * R * 4; }
+
+// v's four rows of 16 lanes, each broadcast to all four rows.
+__device__ __forceinline__ void broadcast_rows(uint32_t v, uint32_t out[4]) {
+  const auto half = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  const auto a = __builtin_amdgcn_permlane16_swap(half[0], half[0], false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(half[1], half[1], false, false);
+  out[0] = a[0];
+  out[1] = a[1];
+  out[2] = b[0];
+  out[3] = b[1];
+}
+
+// One word's four blocks in registers for this lane: per block the 16 code
+// bytes that hold the lane's 16 levels and the entry's class, the scale of the
+// lane's own position, and the activations of the word's columns.
+template <int RB>
+struct MmWord {
+  static constexpr int kCols = 4 / RB;
+  u32x4 w[4];
+  uint32_t c[4];  // the class's row of the decoding constants
+  uint32_t s;
+  u32x4 a[kCols][2];
+};
+
+// X rows 0 .. M-1 (fp16, stride ldx) as a buffer resource (the bytes up to the
+// end of row M-1) and this lane's row l % 16 at the first of its 16 weights.
+struct XRows {
+  __amdgpu_buffer_rsrc_t rsrc;
+  uint32_t row;
+};
+__device__ __forceinline__ XRows mm_x_rows(const uint16_t* x, int64_t ldx, int M, int K, uint32_t lane) {
+  return XRows{__builtin_amdgcn_make_buffer_rsrc((void*)x, 0, (int)(2 * ((int64_t)(M - 1) * ldx + K)), 0x00020000),
+               2u * (uint32_t)((int64_t)min((int)(lane & 15u), M - 1) * ldx + 16 * (int)(lane >> 4))};
+}
+
+// The activations of word w's columns (X through a buffer resource covering
+// the M rows; lanes of rows past M - 1 read row M - 1, whose products are
+// never stored).  Columns past the unit's last one read the last one.
+template <int RB, typename Word>
+__device__ __forceinline__ void load_mm_x(Word& bk, const XRows& xr, int w, int logR, int j0, int cols) {
+  constexpr int NC = Word::kCols;
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int col = min(RB == 4 ? (w << 6) >> logR : w * NC + i, cols - 1);
+    const int xo = 128 * (j0 + col);  // wave-uniform
+    bk.a[i][0] = __builtin_amdgcn_raw_buffer_load_b128(xr.rsrc, (int)xr.row, xo, 0);
+    bk.a[i][1] = __builtin_amdgcn_raw_buffer_load_b128(xr.rsrc, (int)xr.row + 16, xo, 0);
+  }
+}
+
+// Decoding constants of the lanes with h = l / 16 for width class c, 32 bytes a
+// row (h, c) in the wave's LDS (a lookup costs one address and no select):
+//   word 0  field mask of a pair (two codes, one per half-word)
+//   word 1  -(offset) 2^-10 in both fp16 halves (offset 1 for 1 bit, else 2^(b-1))
+//   word 2  the factor that makes a masked field u (an fp16 subnormal, u 2^-24)
+//           u 2^-10 (2u 2^-10 for 1 bit): 2^14 (2^15) in both halves
+//   word 3  b in the low byte, then the first field's bit offset (1-bit codes of
+//           odd h are fields 8 .. 15 of their word)
+//   word 4  byte offset of the lane's codes in the entry, less c (which the
+//           entry's code offset carries in its low bits)
+constexpr float kMmUnit = 1024.0f;  // levels are made as q 2^-10: the sums are multiplied by this at the end
+
+__device__ __forceinline__ void write_mm_table(uint32_t tab, uint32_t lane) {
+  const uint32_t h = lane >> 2, c = lane & 3u, b = 1u << c;
+  const uint32_t mask = (1u << b) - 1u;
+  const uint32_t off = c == 0u ? 0x9400u : c == 1u ? 0x9800u : c == 2u ? 0xA000u : 0xB000u;
+  const uint32_t mul = c == 0u ? 0x7800u : 0x7400u;
+  const uint32_t first = c == 0u ? 8u * (h & 1u) : 0u;
+  if (lane < 16u) {
+    lds_store_u32x4(tab + 32u * lane,
+                    u32x4{mask * 0x00010001u, off * 0x00010001u, mul * 0x00010001u, b | (first << 8)});
+    lds_store_u32(tab + 32u * lane + 16u, (((2u * h) << c) & ~3u) - c);
+  }
+}
+
+// The lane's levels 16h .. 16h + 15 are pairs 8h .. 8h + 7, whose codes start at
+// byte (2h << c) & ~3 of the entry.  htab: the lane's rows of the table.
+template <int RB>
+__device__ __forceinline__ void load_mm_word(MmWord<RB>& bk, const DevMatrix& mat, const LaneEntry& e, uint32_t htab) {
+  bk.s = (uint32_t)ld<uint16_t>(mat.blob, e.scale);
+  uint32_t ac[4];
+  broadcast_rows(e.codes, ac);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    bk.c[i] = htab + 32u * (ac[i] & 7u);
+    bk.w[i] = ld<u32x4>(mat.blob, ac[i] + lds_u32(bk.c[i] + 16u));
+  }
+}
+
+// D 2^-10 of one block: two 16 x 16 x 32 products (weights 16h .. 16h + 7 and
+// 16h + 8 .. 16h + 15 of the lane's entry against the same activations).  The
+// lane's pairs are consecutive fields: eight of one word at 1 and 2 bits, four
+// of two words at 4, two of four at 8.  A masked field is an fp16 subnormal, and
+// one packed fp16 FMA makes the level q 2^-10 exactly.  (VALU time per pair on
+// the card: shift 1.05 + and 1.05 + packed FMA 1.85 ns; with the field ORed into
+// 1024.0 and a packed add, and per-pair shift amounts, it was 4.8 + 1.9.)
+__device__ __forceinline__ float4_t mm_products(const u32x4& w, uint32_t row, const u32x4& a0, const u32x4& a1) {
+  const u32x4 k = lds_u32x4(row);
+  const uint32_t b = k.w & 31u;
+  const bool is8 = k.x >= 0x00FF00FFu, is4 = k.x >= 0x000F000Fu;  // (8 bits before 4)
+  uint32_t t[8];
+  t[0] = w.x >> (k.w >> 8);
+  t[1] = t[0] >> b;
+  t[2] = is8 ? w.y : t[1] >> b;
+  t[3] = t[2] >> b;
+  t[4] = is8 ? w.z : is4 ? w.y : t[3] >> b;
+  t[5] = t[4] >> b;
+  t[6] = is8 ? w.w : t[5] >> b;
+  t[7] = t[6] >> b;
+  uint32_t q[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    q[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(as_h2(t[i] & k.x), as_h2(k.z), as_h2(k.y)));
+  const half8_t b0 = __builtin_bit_cast(half8_t, u32x4{q[0], q[1], q[2], q[3]});
+  const half8_t b1 = __builtin_bit_cast(half8_t, u32x4{q[4], q[5], q[6], q[7]});
+  float4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
+  d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), b0, d, 0, 0, 0);
+  d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), b1, d, 0, 0, 0);
+  return d;
+}
+
+// acc += s * D over the word's blocks; word w's block i is row block i (R >= 64),
+// i % 2 (32) or 0 (16) of the slice's rows.  Blocks of columns past the unit's
+// last one (nblocks of 4 are real) add nothing.
+template <int RB>
+__device__ __forceinline__ void mm_word(const MmWord<RB>& bk, int nblocks, float4_t (&acc)[RB]) {
+  uint32_t sb[4];
+  broadcast_rows(bk.s, sb);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (RB == 4 || i < nblocks) {  // wave-uniform
+      float s = (float)__builtin_bit_cast(_Float16, (uint16_t)sb[i]);
+      __asm__("" : "+v"(s));  // converted once (a mixed-precision FMA would convert it four times at half rate)
+      const float4_t d = mm_products(bk.w[i], bk.c[i], bk.a[i / RB][0], bk.a[i / RB][1]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i % RB][j] = __builtin_fmaf(s, d[j], acc[i % RB][j]);
+    }
+  }
+}
+
+// One-width matrices (class UNI): entries sit at consecutive real positions, so
+// there is no width map, no lookup and no constants to read.
+template <int RB, int UNI>
+struct MmUniWord {
+  static constexpr int kCols = 4 / RB;
+  static constexpr int kWords = UNI == 3 ? 4 : UNI == 2 ? 2 : 1;  // words that hold the lane's 16 levels
+  uint32_t w[4][kWords];
+  uint32_t s;
+  u32x4 a[kCols][2];
+};
+
+// Word w of a unit whose first entry is `first`; the entry at (column, row) is
+// first + column * rows + row.  Rows and columns past the real ones read the
+// last real one (their products are never stored, or not made).
+template <int RB, int UNI>
+__device__ __forceinline__ void load_mm_uni_word(MmUniWord<RB, UNI>& bk, const DevMatrix& mat, const UnitInfo& u,
+                                                 uint32_t first, int w, uint32_t lane) {
+  const uint32_t lim = max(mat.n_entries[UNI], 1u) - 1u;
+  const uint32_t n = lane & 15u, h = lane >> 4;
+  const uint32_t hoff = UNI == 0 ? 4u * (h >> 1) : (2u << UNI) * h;
+  {
+    const int p = 64 * w + (int)lane;
+    const int col = min(p >> mat.logR, u.cols - 1), row = min(p & (mat.R - 1), u.rows - 1);
+    const uint32_t g = min(first + (uint32_t)(col * u.rows + row), lim);
+    bk.s = (uint32_t)ld<uint16_t>(mat.blob, mat.off_scales[UNI] + 2u * g);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int p = 64 * w + 16 * i;  // wave-uniform
+    const int col = min(p >> mat.logR, u.cols - 1), row0 = p & (mat.R - 1);
+    const uint32_t row = (uint32_t)min(row0 + (int)n, u.rows - 1);
+    const uint32_t g = min(first + (uint32_t)(col * u.rows) + row, lim);
+    const uint32_t off = mat.off_codes[UNI] + g * (8u << UNI) + hoff;
+    if constexpr (UNI <= 1) {
+      bk.w[i][0] = ld<uint32_t>(mat.blob, off);
+    } else if constexpr (UNI == 2) {
+      const u32x2 v = ld<u32x2>(mat.blob, off);
+      bk.w[i][0] = v.x;
+      bk.w[i][1] = v.y;
+    } else {
+      const u32x4 v = ld<u32x4>(mat.blob, off);
+      bk.w[i][0] = v.x;
+      bk.w[i][1] = v.y;
+      bk.w[i][2] = v.z;
+      bk.w[i][3] = v.w;
+    }
+  }
+}
+
+template <int RB, int UNI>
+__device__ __forceinline__ void mm_uni_word(const MmUniWord<RB, UNI>& bk, int nblocks, uint32_t h, float4_t (&acc)[RB]) {
+  constexpr uint32_t b = 1u << UNI, kFields = 16 / b;
+  constexpr uint32_t mask = ((1u << b) - 1u) * 0x00010001u;
+  constexpr uint32_t mul = UNI == 0 ? 0x78007800u : 0x74007400u;
+  constexpr uint32_t off = UNI == 0 ? 0x94009400u : UNI == 1 ? 0x98009800u : UNI == 2 ? 0xA000A000u : 0xB000B000u;
+  uint32_t sb[4];
+  broadcast_rows(bk.s, sb);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (RB == 4 || i < nblocks) {  // wave-uniform
+      float s = (float)__builtin_bit_cast(_Float16, (uint16_t)sb[i]);
+      __asm__("" : "+v"(s));
+      uint32_t q[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t word = UNI == 0 ? bk.w[i][0] >> (8u * (h & 1u)) : bk.w[i][j / kFields];
+        const uint32_t u = (word >> (b * (j % kFields))) & mask;
+        q[j] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(as_h2(u), as_h2(mul), as_h2(off)));
+      }
+      const half8_t b0 = __builtin_bit_cast(half8_t, u32x4{q[0], q[1], q[2], q[3]});
+      const half8_t b1 = __builtin_bit_cast(half8_t, u32x4{q[4], q[5], q[6], q[7]});
+      float4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
+      d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, bk.a[i / RB][0]), b0, d, 0, 0, 0);
+      d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, bk.a[i / RB][1]), b1, d, 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i % RB][j] = __builtin_fmaf(s, d[j], acc[i % RB][j]);
+    }
+  }
+}
+
+// As for the one-row kernel, the values the first loads depend on come as
+// preloaded leading arguments (geo packs R, C, log2 R and S the same way; for
+// one-width matrices the map arguments carry the class's code offset, scale
+// offset and entry count), the
+// unit table is read beside the width map rather than after it, and the
+// argument block is read only once those loads are issued.
+template <int NW, int RB, int UNI = -1>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 16 ? 4 : 2))) void vbq_mm_kernel(
+    const uint8_t* __restrict__ blob, uint32_t off_wmap, uint32_t tile_words, uint32_t chunk_words, uint32_t wmap_words,
+    int32_t G, int32_t N, uint32_t geo, int32_t U, int32_t M, MmArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  DevMatrix mat = a.m;
+  mat.blob = blob;
+  if constexpr (UNI >= 0) {
+    mat.off_codes[UNI] = off_wmap;
+    mat.off_scales[UNI] = tile_words;
+    mat.n_entries[UNI] = chunk_words;
+  } else {
+    mat.off_wmap = off_wmap;
+    mat.tile_words = tile_words;
+    mat.chunk_words = chunk_words;
+  }
+  mat.wmap_words = wmap_words;
+  mat.G = G;
+  mat.N = N;
+  mat.U = U;
+  mat.R = (int)(geo & 0x1FF);
+  mat.C = (int)((geo >> 9) & 0xFF);
+  mat.logR = (int)((geo >> 17) & 0xF);
+  const int R = mat.R, S = (int)(geo >> 21);
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)smem;
+  const int wave = wave_id();
+  const int t = blockIdx.x;  // one row tile per workgroup
+  const int wbytes = mm_wave_bytes(R, M);
+  const uint32_t tab = lds0 + (uint32_t)(wave * wbytes), ysum = tab + kMmTableBytes;
+  const uint32_t lane = lane_id();
+  const uint32_t h = lane >> 4;
+  const uint32_t htab = tab + 128u * h;
+  const int step = RB == 4 ? R >> 6 : 1;  // words of one column = 64-row groups of the tile
+  for (int rg = 0; rg < step; ++rg) {
+    float4_t acc[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) acc[i] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int item = wave; item < mat.U * S; item += NW) {
+      const int k = item / S, sl = item - k * S;
+      const UnitInfo u = load_unit(mat, t, k);
+      const int unit = t * mat.U + k;
+      int cb, ce;
+      slice_cols(u.cols, R, sl, S, cb, ce);
+      if (cb >= ce) continue;  // wave-uniform: an empty slice
+      const int wb = (cb * R) >> 6, we = (ce * R + 63) >> 6;
+      // The words of one range, the next one in flight while one is multiplied.
+      auto walk = [&](auto& A, auto& B, int f, int n, auto&& load, auto&& mul) __attribute__((always_inline)) {
+        if (f >= n) return;
+        load(A, f);
+        int w = f;
+        for (; w + 2 * step < n; w += 2 * step) {
+          load(B, w + step);
+          mul(A, w);
+          load(A, w + 2 * step);
+          mul(B, w + step);
+        }
+        if (w + step < n) {
+          load(B, w + step);
+          mul(A, w);
+          mul(B, w + step);
+        } else {
+          mul(A, w);
+        }
+      };
+      auto nblocks = [&](int w) __attribute__((always_inline)) { return RB == 4 ? 4 : min(4, (u.cols - w * (4 / RB)) * RB); };
+      if constexpr (UNI >= 0) {
+        const XRows xr = mm_x_rows(a.x, a.ldx, M, mat.K, lane);
+        const uint32_t first = (uint32_t)t * (uint32_t)(R * mat.G) + (uint32_t)u.j0 * (uint32_t)u.rows;
+        MmUniWord<RB, UNI> A, B;
+        walk(A, B, wb + rg, we,
+             [&](MmUniWord<RB, UNI>& b, int w) __attribute__((always_inline)) {
+               load_mm_uni_word<RB, UNI>(b, mat, u, first, w, lane);
+               load_mm_x<RB>(b, xr, w, mat.logR, u.j0, u.cols);
+             },
+             [&](const MmUniWord<RB, UNI>& b, int w) __attribute__((always_inline)) {
+               mm_uni_word<RB, UNI>(b, nblocks(w), h, acc);
+             });
+      } else {
+        const u32x16 rows2 = unit_rows_vec(mat, unit);  // beside the width map, not after it
+        uint32_t start[4] = {rows2.s0, rows2.s1, rows2.s2, rows2.s3};
+        for (int w0 = 0; w0 < we; w0 += 64) {
+          const WordScan sc = scan_words(mat, u, w0, lane);
+          // values from the kernel-argument block only after the loads above are
+          // issued (the compiler would otherwise hoist them and wait for the block)
+          lds_phase();
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            mat.off_codes[c] = opaque(mat.off_codes[c]);
+            mat.off_scales[c] = opaque(mat.off_scales[c]);
+            mat.n_entries[c] = opaque(mat.n_entries[c]);
+          }
+          const XRows xr = mm_x_rows((const uint16_t*)opaque64((uint64_t)a.x), (int64_t)opaque64((uint64_t)a.ldx), M, mat.K,
+                                     lane);
+          write_mm_table(tab, lane);
+          lds_phase();
+          MmWord<RB> A, B;
+          walk(A, B, max(wb, w0) + rg, min(we, w0 + 64),
+               [&](MmWord<RB>& b, int w) __attribute__((always_inline)) {
+                 load_mm_x<RB>(b, xr, w, mat.logR, u.j0, u.cols);
+                 load_mm_word<RB>(b, mat, word_entries(mat, u, sc, start, w0, w - w0), htab);
+               },
+               [&](const MmWord<RB>& b, int w) __attribute__((always_inline)) { mm_word<RB>(b, nblocks(w), acc); });
+          start[0] += sc.t01 & 0xFFFFu;
+          start[1] += sc.t01 >> 16;
+          start[2] += sc.t23 & 0xFFFFu;
+          start[3] += sc.t23 >> 16;
+        }
+      }
+    }
+    // this wave's share of the row sums
+    if (4 * (int)h < M) {
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          lds_store_f32(ysum + 4u * (uint32_t)((4 * (int)h + j) * R + rg * 64 + i * 16 + (int)(lane & 15u)), acc[i][j]);
+    }
+  }
+  __syncthreads();
+  const int rows = min(R, mat.N - t * R);
+  for (int slot = threadIdx.x; slot < M * R; slot += NW * 64) {
+    const int m = slot >> mat.logR, r = slot & (R - 1);
+    if (r < rows) {
+      float tot = 0.0f;
+#pragma unroll
+      for (int w2 = 0; w2 < NW; ++w2) tot += lds_f32(lds0 + (uint32_t)(w2 * wbytes + kMmTableBytes) + 4u * (uint32_t)slot);
+      store_y(a.y, m * a.ldy + (size_t)t * R + r, tot * kMmUnit, a.yf16);
+    }
+  }
 }
 
 // w_hat = s*q written densely.  Bound by the stores (256 bytes a group).  A
@@ -1997,6 +2108,17 @@ bool choose_shape(const DevMatrix& m, int MT, MvShape* sh) {
   return true;
 }
 
+// The one width class of a matrix, or -1 when it has several.
+int one_class(const DevMatrix& m) {
+  int uni = -1, classes = 0;
+  for (int c = 0; c < 4; ++c)
+    if (m.n_entries[c]) {
+      uni = c;
+      ++classes;
+    }
+  return classes == 1 ? uni : -1;
+}
+
 // Raises a kernel's dynamic LDS limit once per device.
 vbq_status allow_big_lds(const void* kernel, std::atomic<uint64_t>& done) {
   int dev = 0;
@@ -2128,13 +2250,8 @@ vbq_status launch_mv(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
   a.ylen = ylen;
   if constexpr (MT == 1) {
     // a matrix of one width class (a "recipe" matrix) takes the uniform kernel
-    int uni = -1, classes = 0;
-    for (int c = 0; c < 4; ++c)
-      if (m.n_entries[c]) {
-        uni = c;
-        ++classes;
-      }
-    if (classes == 1) {
+    const int uni = one_class(m);
+    if (uni >= 0) {
       // no position index; the 1-bit kernel holds one group column's lookup
       // tables per wave
       sh.lds = mv_lds_bytes(m.R, sh.SW, 1, sh.NW, uni == 0 ? kLutBytes : 0, false);
@@ -2164,9 +2281,9 @@ vbq_status launch_mv(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
 
 // Several rows on matrix cores: same item split as the one-row path (slices
 // of at most 32 columns, at least four items per tile).
-template <int NW, int RB>
+template <int NW, int RB, int UNI>
 vbq_status launch_mm_nw(const MmArgs& a, int lds, hipStream_t s) {
-  const void* kernel = (const void*)vbq_mm_kernel<NW, RB>;
+  const void* kernel = (const void*)vbq_mm_kernel<NW, RB, UNI>;
   if (lds > 64 * 1024) {
     static std::atomic<uint64_t> done{0};
     vbq_status st = allow_big_lds(kernel, done);
@@ -2175,36 +2292,49 @@ vbq_status launch_mm_nw(const MmArgs& a, int lds, hipStream_t s) {
   MmArgs args = a;
   const uint8_t* blob = a.m.blob;
   uint32_t off_wmap = a.m.off_wmap, tile_words = a.m.tile_words, chunk_words = a.m.chunk_words;
+  if constexpr (UNI >= 0) {  // (the kernel reads them as such)
+    off_wmap = a.m.off_codes[UNI];
+    tile_words = a.m.off_scales[UNI];
+    chunk_words = a.m.n_entries[UNI];
+  }
   uint32_t wmap_words = a.m.wmap_words;
-  int32_t G = a.m.G, N = a.m.N, U = a.m.U;
-  // bit 31: each item's set-up (width map, class runs, index) at a raised issue
-  // priority, for up to eight rows (1.46B-class step: M = 4 1271 -> 1260 us, M = 8
-  // 1343 -> 1326 us; at M = 16 it was slower, 1548 -> 1555 us)
-  uint32_t geo = (uint32_t)a.m.R | ((uint32_t)a.m.C << 9) | ((uint32_t)a.m.logR << 17) | ((uint32_t)a.S << 21) |
-                 (a.M <= 8 ? 1u << 31 : 0u);
-  void* kargs[] = {&blob, &off_wmap, &tile_words, &chunk_words, &wmap_words, &G, &N, &geo, &U, &args};
+  int32_t G = a.m.G, N = a.m.N, U = a.m.U, M = a.M;
+  uint32_t geo = (uint32_t)a.m.R | ((uint32_t)a.m.C << 9) | ((uint32_t)a.m.logR << 17) | ((uint32_t)a.S << 21);
+  void* kargs[] = {&blob, &off_wmap, &tile_words, &chunk_words, &wmap_words, &G, &N, &geo, &U, &M, &args};
   return hip_status(hipLaunchKernel(kernel, dim3((unsigned)a.m.T), dim3(NW * 64), kargs, (size_t)lds, s));
 }
 
-template <int RB>
+template <int RB, int UNI>
 vbq_status launch_mm_rb(const MmArgs& a, int NW, int lds, hipStream_t s) {
-  if (NW == 4) return launch_mm_nw<4, RB>(a, lds, s);
-  if (NW == 8) return launch_mm_nw<8, RB>(a, lds, s);
-  return launch_mm_nw<16, RB>(a, lds, s);
+  if (NW == 4) return launch_mm_nw<4, RB, UNI>(a, lds, s);
+  return launch_mm_nw<8, RB, UNI>(a, lds, s);
+}
+
+template <int RB>
+vbq_status launch_mm_uni(const MmArgs& a, int uni, int NW, int lds, hipStream_t s) {
+  switch (uni) {
+    case 0: return launch_mm_rb<RB, 0>(a, NW, lds, s);
+    case 1: return launch_mm_rb<RB, 1>(a, NW, lds, s);
+    case 2: return launch_mm_rb<RB, 2>(a, NW, lds, s);
+    case 3: return launch_mm_rb<RB, 3>(a, NW, lds, s);
+    default: return launch_mm_rb<RB, -1>(a, NW, lds, s);
+  }
 }
 
 // Launch shape of the matrix-core kernel: waves per workgroup, slices per
-// unit, LDS bytes.  Each wave walks its blocks one after the other, so small
-// matrices split their tiles over more waves, as long as the whole grid fits
-// the GPU at once (about 20 waves per CU at this kernel's register use).
-bool mm_shape(const DevMatrix& m, int* NWo, int* So, int* ldso) {
+// unit, LDS bytes.  Each wave walks its words one after the other, so small
+// matrices split their tiles over more waves, up to eight (sixteen waves of a
+// workgroup leave a wave 128 registers: 2048 x 2048 M = 4 took 8.1 us against
+// 4.3), as long as the whole grid fits the GPU at once (about 20 waves per CU
+// at this kernel's register use).
+bool mm_shape(const DevMatrix& m, int M, int* NWo, int* So, int* ldso) {
   int NWt = kMinWaves;
-  while (NWt < 16 && (int64_t)m.T * NWt * 2 <= 256 * 20) NWt *= 2;
+  while (NWt < 8 && (int64_t)m.T * NWt * 2 <= 256 * 20) NWt *= 2;
   int S = (NWt + m.U - 1) / m.U;
   while (max_slice_cols(m.R, m.C, S) > kMmMaxCols) ++S;
-  const int wbytes = mm_wave_bytes(m.R, max_slice_cols(m.R, m.C, S));
+  const int wbytes = mm_wave_bytes(m.R, M);
   int NW = kMinWaves;  // (fewer waves than items is fine: items are dealt in turn)
-  while (NW < 16 && NW < m.U * S && 2 * NW * wbytes <= kLdsLimit) NW *= 2;
+  while (NW < 8 && NW < m.U * S && 2 * NW * wbytes <= kLdsLimit) NW *= 2;
   *NWo = NW;
   *So = S;
   *ldso = NW * wbytes;
@@ -2214,7 +2344,7 @@ bool mm_shape(const DevMatrix& m, int* NWo, int* So, int* ldso) {
 vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t ldx, int M, void* y, int64_t ldy,
                      hipStream_t s) {
   int NW, S, lds;
-  if (!mm_shape(m, &NW, &S, &lds)) return VBQ_ERR_UNSUPPORTED;
+  if (!mm_shape(m, M, &NW, &S, &lds)) return VBQ_ERR_UNSUPPORTED;
   MmArgs a;
   a.m = m;
   a.x = (const uint16_t*)x;
@@ -2225,13 +2355,23 @@ vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
   a.S = S;
   a.yf16 = (flags & VBQ_Y_F16) ? 1 : 0;
   // row blocks of 16 per group: one, two or four (R = 16, 32, >= 64)
-  if (m.R == 16) return launch_mm_rb<1>(a, NW, lds, s);
-  if (m.R == 32) return launch_mm_rb<2>(a, NW, lds, s);
-  return launch_mm_rb<4>(a, NW, lds, s);
+  const int uni = one_class(m);
+  if (m.R == 16) return launch_mm_uni<1>(a, uni, NW, lds, s);
+  if (m.R == 32) return launch_mm_uni<2>(a, uni, NW, lds, s);
+  return launch_mm_uni<4>(a, uni, NW, lds, s);
 }
 
-// Name of the kernel a product with M activation rows launches on this matrix
-// (the same choices as launch_mv / launch_mm); static storage.
+// Two rows on the matrix cores: one-width matrices and grids beyond the wave-pair
+// kernel's (without the flag that asks for the one-wave kernel).  The two-row
+// dot-product kernel reads x from LDS for every group of each row: 12301 x 2112
+// mixed 16.4 us against 9.8 here, 50304 x 2048 mixed 24.6 against 17.5, 2048 x
+// 8192 2-bit 9.4 against 6.7, 512 x 512 2-bit 5.0 against 2.7.  Smaller mixed
+// grids stay with the wave-pair kernel (or, with more than four units a tile,
+// the one-wave one), whose results the one-wave flag reproduces bit for bit.
+bool takes_mm(const DevMatrix& m, uint32_t flags) {
+  return !(flags & VBQ_ONE_WAVE_PER_UNIT) && (one_class(m) >= 0 || (int64_t)m.T * m.U > kPairMaxUnits);
+}
+
 // The one-launch plan of a bucketed GEMV (vbq_buckets_kernel<4>): every bucket
 // a one-width matrix that the four-wave one-width kernel takes, two or more
 // buckets, all with the same call options, every bucket's blob 256-byte
@@ -2253,14 +2393,9 @@ bool plan_buckets(const vbq_bucket* bk, int n, const void* blob, const int32_t* 
   for (int k = 0; k < n; ++k) {
     const int i = order[k];
     const DevMatrix& m = ms[i];
-    int uni = -1, classes = 0;
-    for (int c = 0; c < 4; ++c)
-      if (m.n_entries[c]) {
-        uni = c;
-        ++classes;
-      }
+    const int uni = one_class(m);
     MvShape sh;
-    if (classes != 1 || !choose_shape(m, 1, &sh) || sh.NW != 4) return false;
+    if (uni < 0 || !choose_shape(m, 1, &sh) || sh.NW != 4) return false;
     need = std::max(need, mv_lds_bytes(m.R, sh.SW, 1, 4, uni == 0 ? kLutBytes : 0, false));
     ba->m[k] = m;
     ba->rows[k] = rows + bk[i].row_begin;
@@ -2279,44 +2414,38 @@ bool plan_buckets(const vbq_bucket* bk, int n, const void* blob, const int32_t* 
   return true;
 }
 
+// Name of the kernel a product with M activation rows launches on this matrix
+// (the same choices as launch_mv / launch_mm); static storage.
 const char* kernel_name(const DevMatrix& m, uint32_t flags, int M) {
-  // (template arguments as the compiler prints them, spaces removed; the
-  // uniform kernel's last argument is the width class log2 b)
-  static const char* const kNames[] = {
-      "vbq_mv_pair_kernel<8,1>", "vbq_mv_pair_kernel<16,1>", "vbq_mv_pair_kernel<8,2>",
-      "vbq_mv_kernel<1,4>", "vbq_mv_kernel<1,8>", "vbq_mv_kernel<1,16>",
-      "vbq_mv_kernel<2,4>", "vbq_mv_kernel<2,8>",
-      "vbq_mv_kernel<1,4,0>", "vbq_mv_kernel<1,8,0>", "vbq_mv_kernel<1,16,0>",
-      "vbq_mv_kernel<1,4,1>", "vbq_mv_kernel<1,8,1>", "vbq_mv_kernel<1,16,1>",
-      "vbq_mv_kernel<1,4,2>", "vbq_mv_kernel<1,8,2>", "vbq_mv_kernel<1,16,2>",
-      "vbq_mv_kernel<1,4,3>", "vbq_mv_kernel<1,8,3>", "vbq_mv_kernel<1,16,3>",
-      "vbq_mm_kernel<4,1>", "vbq_mm_kernel<8,1>", "vbq_mm_kernel<16,1>",
-      "vbq_mm_kernel<4,2>", "vbq_mm_kernel<8,2>", "vbq_mm_kernel<16,2>",
-      "vbq_mm_kernel<4,4>", "vbq_mm_kernel<8,4>", "vbq_mm_kernel<16,4>",
-      "none"};
-  auto nw_index = [](int NW) { return NW == 4 ? 0 : NW == 8 ? 1 : 2; };
-  if (M <= 0) return kNames[29];
-  if (M <= 2) {
+  // (template arguments as the compiler prints them, spaces removed; a one-width
+  // kernel's last argument is the width class log2 b)
+  static const char* const kPair[] = {"vbq_mv_pair_kernel<8,1>", "vbq_mv_pair_kernel<16,1>", "vbq_mv_pair_kernel<8,2>"};
+  static const char* const kMv[5][3] = {{"vbq_mv_kernel<1,4,0>", "vbq_mv_kernel<1,8,0>", "vbq_mv_kernel<1,16,0>"},
+                                        {"vbq_mv_kernel<1,4,1>", "vbq_mv_kernel<1,8,1>", "vbq_mv_kernel<1,16,1>"},
+                                        {"vbq_mv_kernel<1,4,2>", "vbq_mv_kernel<1,8,2>", "vbq_mv_kernel<1,16,2>"},
+                                        {"vbq_mv_kernel<1,4,3>", "vbq_mv_kernel<1,8,3>", "vbq_mv_kernel<1,16,3>"},
+                                        {"vbq_mv_kernel<1,4>", "vbq_mv_kernel<1,8>", "vbq_mv_kernel<1,16>"}};
+#define VBQ_MM_NAMES(rb)                                                                                       \
+  {{"vbq_mm_kernel<4," rb ",0>", "vbq_mm_kernel<8," rb ",0>"}, {"vbq_mm_kernel<4," rb ",1>", "vbq_mm_kernel<8," rb ",1>"}, \
+   {"vbq_mm_kernel<4," rb ",2>", "vbq_mm_kernel<8," rb ",2>"}, {"vbq_mm_kernel<4," rb ",3>", "vbq_mm_kernel<8," rb ",3>"}, \
+   {"vbq_mm_kernel<4," rb ">", "vbq_mm_kernel<8," rb ">"}}
+  static const char* const kMm[3][5][2] = {VBQ_MM_NAMES("1"), VBQ_MM_NAMES("2"), VBQ_MM_NAMES("4")};
+#undef VBQ_MM_NAMES
+  if (M <= 0) return "none";
+  const int uni = one_class(m), c = uni < 0 ? 4 : uni;
+  if (M <= 2 && !(M == 2 && takes_mm(m, flags))) {
     if (!(flags & VBQ_ONE_WAVE_PER_UNIT)) {
       const int pw = pair_waves(m, M);
-      if (pw) return kNames[M == 2 ? 2 : pw == 8 ? 0 : 1];
+      if (pw) return kPair[M == 2 ? 2 : pw == 8 ? 0 : 1];
     }
     MvShape sh;
-    if (!choose_shape(m, M, &sh)) return kNames[29];
-    if (M == 2) return kNames[sh.NW == 4 ? 6 : 7];
-    int uni = -1, classes = 0;
-    for (int c = 0; c < 4; ++c)
-      if (m.n_entries[c]) {
-        uni = c;
-        ++classes;
-      }
-    if (classes == 1) return kNames[8 + 3 * uni + nw_index(sh.NW)];
-    return kNames[3 + nw_index(sh.NW)];
+    if (!choose_shape(m, M, &sh)) return "none";
+    if (M == 2) return sh.NW == 4 ? "vbq_mv_kernel<2,4>" : "vbq_mv_kernel<2,8>";
+    return kMv[c][sh.NW == 4 ? 0 : sh.NW == 8 ? 1 : 2];
   }
   int NW, S, lds;
-  if (!mm_shape(m, &NW, &S, &lds)) return kNames[29];
-  const int rb = m.R == 16 ? 0 : m.R == 32 ? 1 : 2;
-  return kNames[20 + 3 * rb + nw_index(NW)];
+  if (!mm_shape(m, M, &NW, &S, &lds)) return "none";
+  return kMm[m.R == 16 ? 0 : m.R == 32 ? 1 : 2][c][NW == 4 ? 0 : 1];
 }
 
 // ---------------------------------------------------------------------------
@@ -2709,7 +2838,9 @@ vbq_status vbq_gemm_small(const vbq_desc* desc, const void* blob_dev, int64_t M,
   const int Mi = (int)M;
   const uint32_t f = desc->flags;
   if (Mi == 1) return launch_mv<1>(m, f, X_dev, ldx, 1, Y_dev, ldy, s);
-  if (Mi == 2) return launch_mv<2>(m, f, X_dev, ldx, 2, Y_dev, ldy, s);
+  // (the matrix-core kernel addresses X with 32-bit offsets)
+  if (Mi == 2 && !(takes_mm(m, f) && ldx + desc->K < (1ll << 30)))
+    return launch_mv<2>(m, f, X_dev, ldx, 2, Y_dev, ldy, s);
   return launch_mm(m, f, X_dev, ldx, Mi, Y_dev, ldy, s);
 }
 

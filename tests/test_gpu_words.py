@@ -12,6 +12,7 @@ torch = pytest.importorskip("torch")
 
 from oracle import matmul as omatmul  # noqa: E402
 from paper_2607_02893_amd import synth  # noqa: E402
+from tests import parity  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -47,3 +48,31 @@ def test_dequant_exact_and_unaligned(vbq, N, K, R, C, uniform):
     assert st == 0
     assert torch.equal(out.cpu().view(N, K), want)
     assert buf[0].item() == 7.0 and torch.all(buf[1 + N * K:] == 7.0)  # nothing written outside
+
+
+# the matrix-core product: also a grid beyond the wave-pair kernel's (two rows)
+MM_GEOMS = GEOMS[:6] + [(33000, 256, 16, 1)]
+
+
+@pytest.mark.parametrize("uniform", [0, 1, 2, 4, 8])
+@pytest.mark.parametrize("M", [2, 5, 16])
+@pytest.mark.parametrize("N,K,R,C", MM_GEOMS)
+def test_batch_products_within_the_float32_bound(vbq, N, K, R, C, M, uniform):
+    """Row 0 of X is a one-hot column (exact: a level times its scale), the others
+    random, within the bound of any float32 order of summation; padded X and Y."""
+    print(f"gemm M={M} N={N} K={K} R={R} C={C} uniform={uniform}", flush=True)
+    Wp, bits, q, s = _packed(vbq, N, K, R, C, uniform)
+    if M > 2 or uniform or Wp.desc.n_units > 2048:
+        assert vbq.kernel_name(Wp.desc, M).startswith("vbq_mm_kernel<")
+    X = synth.draw_x(synth.rng_for(311, M), M, K)
+    X[0] = 0
+    X[0, K - 1] = 1.0
+    Xd = torch.zeros((M, K + 8), dtype=torch.float16, device="cuda")
+    Xd[:, :K] = torch.from_numpy(X).cuda()
+    Yd = torch.full((M, N + 3), 7.0, device="cuda")
+    Wp.gemm_small(Xd[:, :K], Yd[:, :N])
+    Y = Yd.cpu().numpy()
+    assert np.all(Y[:, N:] == 7.0)
+    assert np.array_equal(Y[0, :N].astype(np.float64), omatmul.gemv(q, s, X[0]))
+    for m in (1, M - 1):
+        parity.check_bound(Y[m, :N], omatmul.gemv(q, s, X[m]), parity.fp32_bound(q, s, bits, X[m]), what=f"row {m}")
