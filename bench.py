@@ -293,7 +293,7 @@ def write_traffic_file(path, summ):
 def write_qat_traffic_file(path, summ):
     """Counter summary of the selection-path forward kernel (read back by measured_traffic)."""
     lines = [
-        "# HBM traffic of vbq_qat_forward_kernel: 131M-class training step (one launch)",
+        "# HBM traffic of the fp32 selection forward: 131M-class training step (one launch)",
         "",
         "Two counter passes over `bench.py --qat --profile --steps 2 --warmup 1` (3 forward launches over the",
         "131M-class model's 137.8M linear weights), then a plain copy of 256 MiB (torch.mul by 1.0) to",
@@ -502,14 +502,14 @@ def main_qat(args):
         "pct_of_peak_hbm": round(100 * value / PEAK_HBM_GBS, 1),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": round(achieved / PEAK_HBM_GBS, 4), "traffic": traffic,
-                     "kernel": "vbq_qat_forward_kernel",
+                     "kernel": "vbq_qat_forward_narrow_kernel",
                      "launches_per_step": 1,
                      "algorithmic_bytes_per_launch": int(alg_kernel),
                      "avg_launch_us": round(1e6 * kern_s, 3),
                      "timing": "HIP events on the launch stream around K launches of the kernel alone",
                      "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
                      "traffic_vs_algorithmic": round(traffic / alg_kernel, 3) if traffic else None},
-        "w_soft_bf16": {"kernel": "vbq_qat_forward_kernel<bf16>", "us_per_launch": round(1e6 * k16_s, 2),
+        "w_soft_bf16": {"kernel": "vbq_qat_forward_kernel (bf16)", "us_per_launch": round(1e6 * k16_s, 2),
                         "algorithmic_bytes": int(alg16), "GBps": round(alg16 / k16_s / 1e9, 1),
                         "frac": round(alg16 / k16_s / 1e9 / PEAK_HBM_GBS, 4),
                         "note": "the same forward writing w_soft as bf16 (rounded to nearest even)"},
@@ -554,7 +554,7 @@ def main():
     args = ap.parse_args()
     if args.pmc_summary:
         if args.qat:
-            summ = pmc_summary(*args.pmc_summary, kernel="vbq_qat_forward_kernel", sources=QAT_SOURCES)
+            summ = pmc_summary(*args.pmc_summary, kernel="vbq_qat_forward", sources=QAT_SOURCES)
         else:
             summ = pmc_summary(*args.pmc_summary)
         print(json.dumps(summ), flush=True)

@@ -31,7 +31,9 @@
 //   * the next slab's loads are issued before the current slab's arithmetic;
 //   * the results go back through LDS and out as coalesced 16-byte stores;
 //   * the bulk loads and stores carry the non-temporal hint, and the grid is
-//     2048 one-wave blocks (eight per CU), which measured fastest.
+//     2048 one-wave blocks (eight per CU), which measured fastest;
+//   * few slabs, and fp32 outputs at any count, take the narrow kernels: four
+//     waves to a slab, weights kept in registers (described where they are defined).
 
 #include <hip/hip_runtime.h>
 
@@ -51,6 +53,14 @@ constexpr int kGroupsPerSlab = 64;  // one group per lane
 constexpr int kRowFloats = 68;      // LDS row of one group: 64 weights + 4 floats of padding
 constexpr int kMaxBlocks = 2048;    // one wave per block; eight resident blocks per CU on 256 CUs
 constexpr int kGradBlocks = 2048;   // the gradient's blocks: one tile + a 2 KiB table, eight resident per CU
+// A slab to four waves (the narrow kernels) or to one wave that loads ahead: fp32
+// w_soft always the former (us a launch with bbar, narrow / wide: 4096 groups 6.8 /
+// 10.5, 65551 11.6 / 14.6, 2153472 212 / 223).  bf16 w_soft up to 8192 slabs
+// (524288 groups 55.8 / 56.6, 2153472 195 / 180), the gradient up to 16384 (4096
+// groups 4.7 / 9.0, 65551 9.8 / 12.4, 1048576 102.8 / 104.7, 2153472 210 / 204).
+constexpr int64_t kNarrowBf16Slabs = 8192;
+constexpr int64_t kNarrowGradSlabs = 16384;
+constexpr int kNarrowGradBlocks = 4096;
 constexpr int kBbarThreads = 256;
 constexpr float kMinTau = 1.17549435e-38f;  // the smallest normal float: a subnormal tau may be flushed to 0
 constexpr uint32_t kRsrcFlags = 0x00020000;
@@ -90,7 +100,6 @@ __device__ __forceinline__ float fp16_from_double(double d) {
 struct Cand {   // one candidate width of one group
   float s;      // stored scale (an fp16 value), 0 for an all-zero group
   float r;      // approximate 1/s (0 when s == 0)
-  float c;      // pi_k * s
   float qmax;
 };
 
@@ -182,7 +191,7 @@ struct QatArgs {
   const float* W;
   const float* logits;
   const float* noise;  // may be null
-  void* w_soft;        // float, or bf16 with kBf16
+  void* w_soft;        // float, or bf16
   float* pi;           // may be null
   uint8_t* hard;       // may be null
   double* partial;     // per-block sums of sum_k pi_k B_k, or null
@@ -197,7 +206,50 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-template <bool kBf16>
+// Gumbel-Softmax weights of a group (section 3.2); the largest l + e is subtracted
+// before the division, so a small tau cannot overflow to inf - inf.
+struct Mix {
+  float p0, p1, p2, p3;
+  __device__ __forceinline__ float bits() const { return p0 + 2.0f * p1 + 4.0f * p2 + 8.0f * p3; }
+};
+__device__ __forceinline__ Mix softmax_mix(const u32x4& lg, const u32x4& ns, float tau) {
+  const float v0 = __uint_as_float(lg.x) + __uint_as_float(ns.x), v1 = __uint_as_float(lg.y) + __uint_as_float(ns.y);
+  const float v2 = __uint_as_float(lg.z) + __uint_as_float(ns.z), v3 = __uint_as_float(lg.w) + __uint_as_float(ns.w);
+  const float vm = __builtin_fmaxf(__builtin_fmaxf(v0, v1), __builtin_fmaxf(v2, v3));
+  const float p0 = expf((v0 - vm) / tau), p1 = expf((v1 - vm) / tau), p2 = expf((v2 - vm) / tau), p3 = expf((v3 - vm) / tau);
+  const float psum = (p0 + p1) + (p2 + p3);
+  return Mix{p0 / psum, p1 / psum, p2 / psum, p3 / psum};
+}
+
+// pi and the hardened width (Algorithm 1's result: the width of the largest
+// logit, the first of equal maxima) of group g0 + i.
+__device__ __forceinline__ void store_group_outputs(const QatArgs& a, int64_t g0, uint32_t ng, uint32_t i, const u32x4& lg,
+                                                    const Mix& m) {
+  if (a.pi) {
+    const u32x4 pv = {__float_as_uint(m.p0), __float_as_uint(m.p1), __float_as_uint(m.p2), __float_as_uint(m.p3)};
+    __builtin_amdgcn_raw_buffer_store_b128(pv, rsrc(a.pi + g0 * 4, ng * 16u), (int)(i * 16), 0, 0);
+  }
+  if (a.hard) {
+    const float l1 = __uint_as_float(lg.y), l2 = __uint_as_float(lg.z), l3 = __uint_as_float(lg.w);
+    int k = 0;
+    float best = __uint_as_float(lg.x);
+    if (l1 > best) { best = l1; k = 1; }
+    if (l2 > best) { best = l2; k = 2; }
+    if (l3 > best) { k = 3; }
+    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(1u << k), rsrc(a.hard + g0, ng), (int)i, 0, 0);
+  }
+}
+
+// w_soft of one weight, c_k = pi_k * s_k.
+__device__ __forceinline__ float mix_weight(float x, const Scales& sc, float c1, float c2, float c4, float c8) {
+  float q2, q4, q8;
+  levels(x, sc, q2, q4, q8);
+  float acc = x >= 0.0f ? c1 : -c1;  // sign(0) = +1 (also for -0.0)
+  acc = __builtin_fmaf(c2, q2, acc);
+  acc = __builtin_fmaf(c4, q4, acc);
+  return __builtin_fmaf(c8, q8, acc);
+}
+
 __global__ __launch_bounds__(64) void vbq_qat_forward_kernel(QatArgs a) {
   __shared__ __attribute__((aligned(16))) float tile[kGroupsPerSlab * kRowFloats];
   const uint32_t lane = threadIdx.x;
@@ -232,46 +284,16 @@ __global__ __launch_bounds__(64) void vbq_qat_forward_kernel(QatArgs a) {
 #pragma unroll
     for (int j = 0; j < 16; ++j) lds_store_u32x4(co_addr[j], v[j]);
     __syncthreads();
-    const float l0 = __uint_as_float(lg.x), l1 = __uint_as_float(lg.y);
-    const float l2 = __uint_as_float(lg.z), l3 = __uint_as_float(lg.w);
-    const float e0 = __uint_as_float(ns.x), e1 = __uint_as_float(ns.y);
-    const float e2 = __uint_as_float(ns.z), e3 = __uint_as_float(ns.w);
+    const u32x4 lgc = lg, nsc = ns;
     // ---- the next slab's loads overlap this slab's arithmetic
     if (slab + stride < a.n_slabs) load_slab(slab + stride);
 
     // ---- group statistics and scales (section 3.1), streaming the lane's row
     const Scales sc = group_scales(row_addr);
-    const float s1 = sc.s1;
-    Cand c2 = sc.c2, c4 = sc.c4, c8 = sc.c8;
-
-    // ---- Gumbel-Softmax weights (section 3.2); the largest l + e is subtracted
-    // before the division, so a small tau cannot overflow to inf - inf
-    const float v0 = l0 + e0, v1 = l1 + e1, v2 = l2 + e2, v3 = l3 + e3;
-    const float vm = __builtin_fmaxf(__builtin_fmaxf(v0, v1), __builtin_fmaxf(v2, v3));
-    const float p0 = expf((v0 - vm) / a.tau), p1 = expf((v1 - vm) / a.tau), p2 = expf((v2 - vm) / a.tau),
-                p3 = expf((v3 - vm) / a.tau);
-    const float psum = (p0 + p1) + (p2 + p3);
-    const float pi0 = p0 / psum, pi1 = p1 / psum, pi2 = p2 / psum, pi3 = p3 / psum;
-    const float c1 = pi0 * s1;
-    c2.c = pi1 * c2.s;
-    c4.c = pi2 * c4.s;
-    c8.c = pi3 * c8.s;
-    const bool valid = lane < ng;
-    if (valid) eb_sum += (double)(pi0 + 2.0f * pi1 + 4.0f * pi2 + 8.0f * pi3);
-    if (a.pi) {
-      const u32x4 pv = {__float_as_uint(pi0), __float_as_uint(pi1),
-                        __float_as_uint(pi2), __float_as_uint(pi3)};
-      __builtin_amdgcn_raw_buffer_store_b128(pv, rsrc(a.pi + g0 * 4, ng * 16u), (int)(lane * 16), 0, 0);
-    }
-    if (a.hard) {
-      // Algorithm 1's result: the width of the largest logit (the first of equal maxima)
-      int k = 0;
-      float best = l0;
-      if (l1 > best) { best = l1; k = 1; }
-      if (l2 > best) { best = l2; k = 2; }
-      if (l3 > best) { k = 3; }
-      __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(1u << k), rsrc(a.hard + g0, ng), (int)lane, 0, 0);
-    }
+    const Mix mx = softmax_mix(lgc, nsc, a.tau);
+    const float c1 = mx.p0 * sc.s1, c2 = mx.p1 * sc.c2.s, c4 = mx.p2 * sc.c4.s, c8 = mx.p3 * sc.c8.s;
+    if (lane < ng) eb_sum += (double)mx.bits();
+    store_group_outputs(a, g0, ng, lane, lgc, mx);
 
     // ---- the mix, four weights at a time, in place in the lane's row
 #pragma unroll 2
@@ -279,36 +301,20 @@ __global__ __launch_bounds__(64) void vbq_qat_forward_kernel(QatArgs a) {
       const u32x4 t = lds_u32x4(row_addr + 16u * j);
       float f[4] = {__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w)};
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float x = f[i];
-        float q2, q4, q8;
-        levels(x, sc, q2, q4, q8);
-        float acc = x >= 0.0f ? c1 : -c1;  // sign(0) = +1 (also for -0.0)
-        acc = __builtin_fmaf(c2.c, q2, acc);
-        acc = __builtin_fmaf(c4.c, q4, acc);
-        acc = __builtin_fmaf(c8.c, q8, acc);
-        f[i] = acc;
-      }
+      for (int i = 0; i < 4; ++i) f[i] = mix_weight(f[i], sc, c1, c2, c4, c8);
       const u32x4 o = {__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
       lds_store_u32x4(row_addr + 16u * j, o);
     }
 
     // ---- out of LDS with coalesced stores (bf16: each float rounded to nearest even)
     __syncthreads();
-    if constexpr (kBf16) {
-      const __amdgpu_buffer_rsrc_t ro = rsrc((const uint16_t*)a.w_soft + g0 * 64, ng * 128u);
+    const __amdgpu_buffer_rsrc_t ro = rsrc((const uint16_t*)a.w_soft + g0 * 64, ng * 128u);
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const u32x4 t = lds_u32x4(co_addr[j]);
-        const u32x2 o = {bf16_pair(__uint_as_float(t.x), __uint_as_float(t.y)),
-                         bf16_pair(__uint_as_float(t.z), __uint_as_float(t.w))};
-        __builtin_amdgcn_raw_buffer_store_b64(o, ro, (int)(j * 512 + lane * 8), 0, kNonTemporal);
-      }
-    } else {
-      const __amdgpu_buffer_rsrc_t ro = rsrc((const float*)a.w_soft + g0 * 64, ng * 256u);
-#pragma unroll
-      for (int j = 0; j < 16; ++j)
-        __builtin_amdgcn_raw_buffer_store_b128(lds_u32x4(co_addr[j]), ro, (int)(j * 1024 + lane * 16), 0, kNonTemporal);
+    for (int j = 0; j < 16; ++j) {
+      const u32x4 t = lds_u32x4(co_addr[j]);
+      const u32x2 o = {bf16_pair(__uint_as_float(t.x), __uint_as_float(t.y)),
+                       bf16_pair(__uint_as_float(t.z), __uint_as_float(t.w))};
+      __builtin_amdgcn_raw_buffer_store_b64(o, ro, (int)(j * 512 + lane * 8), 0, kNonTemporal);
     }
     __syncthreads();  // the next slab overwrites the tile
   }
@@ -318,6 +324,132 @@ __global__ __launch_bounds__(64) void vbq_qat_forward_kernel(QatArgs a) {
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) eb_sum += __shfl_xor(eb_sum, d, 64);
     if (lane == 0) a.partial[blockIdx.x] = eb_sum;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The narrow kernels: a workgroup of four waves takes a slab, 16 groups a wave.  A wave that
+// owns a slab alone executes about 2500 instructions in a row, 2.1 ns each while
+// nothing else runs on its SIMD, and that, not memory, is what a launch of a few
+// slabs per SIMD waits for.  Here a wave's weights stay in registers as they were
+// loaded (lane l: weights 4 (l % 16) .. + 3 of group 4 j + l / 16, j = 0 .. 3); they
+// pass through LDS only for the group statistics, a lane per group, whose results
+// come back through the rows that held the weights (s1 s2 s4 s8, r2 r4 r8 -, then
+// pi s or the sums of G q).  Per group that costs more (the statistics run on a
+// quarter of the lanes), but its 62 registers and no second copy of the slab in LDS
+// let eight waves a SIMD hide the loads.
+// ---------------------------------------------------------------------------
+constexpr int kNarrowWaves = 4;
+constexpr int kNarrowGroups = kGroupsPerSlab / kNarrowWaves;  // groups of a wave
+constexpr int kNarrowLoads = kNarrowGroups / 4;
+
+// A wave's LDS operations are executed in order: only the compiler has to keep
+// its lanes' writes before the other lanes' reads.
+__device__ __forceinline__ void wave_phase() { __asm__ __volatile__("" ::: "memory"); }
+
+struct NarrowWave {
+  uint32_t lane, tile;         // LDS: 16 rows of kRowFloats floats
+  int64_t g0;                  // the wave's first group in the slab at hand
+  uint32_t ng;                 // its groups (16, less in a ragged last slab)
+};
+
+__device__ __forceinline__ void narrow_slab(NarrowWave& w, int64_t slab, int64_t n_groups, uint32_t wave) {
+  w.g0 = slab * kGroupsPerSlab + (int64_t)wave * kNarrowGroups;
+  const int64_t left = n_groups - w.g0;
+  w.ng = (uint32_t)(left < 0 ? 0 : left < kNarrowGroups ? left : kNarrowGroups);
+}
+
+// The wave's weights of load j, and the statistics of the group of lane l % 16.
+__device__ __forceinline__ void narrow_load(const NarrowWave& w, const float* base, u32x4 (&v)[kNarrowLoads]) {
+  const __amdgpu_buffer_rsrc_t r = rsrc(base + w.g0 * 64, w.ng * 256u);
+#pragma unroll
+  for (int j = 0; j < kNarrowLoads; ++j)
+    v[j] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(j * 1024 + w.lane * 16), 0, kNonTemporal);
+}
+__device__ __forceinline__ Scales narrow_scales(const NarrowWave& w, const u32x4 (&v)[kNarrowLoads]) {
+#pragma unroll
+  for (int j = 0; j < kNarrowLoads; ++j)
+    lds_store_u32x4(w.tile + 4u * ((4u * j + (w.lane >> 4)) * kRowFloats + 4u * (w.lane & 15u)), v[j]);
+  wave_phase();
+  return group_scales(w.tile + 4u * (w.lane & 15u) * kRowFloats);
+}
+__device__ __forceinline__ Scales table_scales(const u32x4& c0, const u32x4& c1) {
+  Scales sc;
+  sc.s1 = __uint_as_float(c0.x);
+  sc.c2.s = __uint_as_float(c0.y);
+  sc.c4.s = __uint_as_float(c0.z);
+  sc.c8.s = __uint_as_float(c0.w);
+  sc.c2.r = __uint_as_float(c1.x);
+  sc.c4.r = __uint_as_float(c1.y);
+  sc.c8.r = __uint_as_float(c1.z);
+  sc.c2.qmax = 1.0f;
+  sc.c4.qmax = 7.0f;
+  sc.c8.qmax = 127.0f;
+  return sc;
+}
+
+template <bool kBf16>
+__global__ __launch_bounds__(kNarrowWaves * 64) __attribute__((amdgpu_waves_per_eu(8))) void vbq_qat_forward_narrow_kernel(QatArgs a) {
+  __shared__ __attribute__((aligned(16))) float tile[kGroupsPerSlab * kRowFloats];
+  __shared__ double eb_wave[kNarrowWaves];
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  NarrowWave w;
+  w.lane = threadIdx.x & 63u;
+  w.tile = (uint32_t)(size_t)(__attribute__((address_space(3))) float*)tile + wave * (kNarrowGroups * kRowFloats * 4u);
+  double eb_sum = 0.0;
+  for (int64_t slab = blockIdx.x; slab < a.n_slabs; slab += gridDim.x) {
+    narrow_slab(w, slab, a.n_groups, wave);
+    const uint32_t lane = w.lane, grp = lane & 15u;
+    u32x4 v[kNarrowLoads];
+    narrow_load(w, a.W, v);
+    const u32x4 lg = __builtin_amdgcn_raw_buffer_load_b128(rsrc(a.logits + w.g0 * 4, w.ng * 16u), (int)(grp * 16), 0, 0);
+    u32x4 ns = {0, 0, 0, 0};
+    if (a.noise) ns = __builtin_amdgcn_raw_buffer_load_b128(rsrc(a.noise + w.g0 * 4, w.ng * 16u), (int)(grp * 16), 0, 0);
+    const Scales sc = narrow_scales(w, v);
+    const Mix mx = softmax_mix(lg, ns, a.tau);
+    // (the four copies of a group write the same table row; one counts it and stores its outputs)
+    if (lane < w.ng) {
+      eb_sum += (double)mx.bits();
+      store_group_outputs(a, w.g0, w.ng, lane, lg, mx);
+    }
+    const uint32_t own_row = w.tile + 4u * grp * kRowFloats;
+    wave_phase();
+    lds_store_u32x4(own_row, u32x4{__float_as_uint(sc.s1), __float_as_uint(sc.c2.s), __float_as_uint(sc.c4.s),
+                                               __float_as_uint(sc.c8.s)});
+    lds_store_u32x4(own_row + 16u, u32x4{__float_as_uint(sc.c2.r), __float_as_uint(sc.c4.r),
+                                                     __float_as_uint(sc.c8.r), 0u});
+    lds_store_u32x4(own_row + 32u,
+                    u32x4{__float_as_uint(mx.p0 * sc.s1), __float_as_uint(mx.p1 * sc.c2.s),
+                          __float_as_uint(mx.p2 * sc.c4.s), __float_as_uint(mx.p3 * sc.c8.s)});
+    wave_phase();
+#pragma unroll
+    for (int j = 0; j < kNarrowLoads; ++j) {
+      const uint32_t row = w.tile + 4u * (4u * j + (lane >> 4)) * kRowFloats;
+      const Scales gs = table_scales(lds_u32x4(row), lds_u32x4(row + 16u));
+      const u32x4 c = lds_u32x4(row + 32u);
+      const float f[4] = {__uint_as_float(v[j].x), __uint_as_float(v[j].y), __uint_as_float(v[j].z), __uint_as_float(v[j].w)};
+      float o[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        o[i] = mix_weight(f[i], gs, __uint_as_float(c.x), __uint_as_float(c.y), __uint_as_float(c.z), __uint_as_float(c.w));
+      if constexpr (kBf16) {
+        const u32x2 b = {bf16_pair(o[0], o[1]), bf16_pair(o[2], o[3])};
+        __builtin_amdgcn_raw_buffer_store_b64(b, rsrc((const uint16_t*)a.w_soft + w.g0 * 64, w.ng * 128u),
+                                              (int)(j * 512 + lane * 8), 0, kNonTemporal);
+      } else {
+        const u32x4 b = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
+        __builtin_amdgcn_raw_buffer_store_b128(b, rsrc((const float*)a.w_soft + w.g0 * 64, w.ng * 256u),
+                                               (int)(j * 1024 + lane * 16), 0, kNonTemporal);
+      }
+    }
+    wave_phase();
+  }
+  if (a.partial) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) eb_sum += __shfl_xor(eb_sum, d, 64);
+    if (w.lane == 0) eb_wave[wave] = eb_sum;
+    __syncthreads();
+    if (threadIdx.x == 0) a.partial[blockIdx.x] = (eb_wave[0] + eb_wave[1]) + (eb_wave[2] + eb_wave[3]);
   }
 }
 
@@ -350,6 +482,53 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
+// Sums of G q over a group for the four candidates: this lane's four weights,
+// then the group's 16 lanes (fixed order); the row's first lane stores them.
+__device__ __forceinline__ void group_products(const u32x4& t, const u32x4& g, const Scales& sc, uint32_t out,
+                                               uint32_t lane) {
+  const float f[4] = {__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w)};
+  const float gr[4] = {__uint_as_float(g.x), __uint_as_float(g.y), __uint_as_float(g.z), __uint_as_float(g.w)};
+  float d1 = 0.0f, d2 = 0.0f, d4 = 0.0f, d8 = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float q2, q4, q8;
+    levels(f[i], sc, q2, q4, q8);
+    d1 += f[i] >= 0.0f ? gr[i] : -gr[i];  // sign(0) = +1
+    d2 = __builtin_fmaf(gr[i], q2, d2);
+    d4 = __builtin_fmaf(gr[i], q4, d4);
+    d8 = __builtin_fmaf(gr[i], q8, d8);
+  }
+  d1 = row16_sum(d1);
+  d2 = row16_sum(d2);
+  d4 = row16_sum(d4);
+  d8 = row16_sum(d8);
+  if ((lane & 15u) == 0)
+    lds_store_u32x4(out, u32x4{__float_as_uint(d1), __float_as_uint(d2), __float_as_uint(d4), __float_as_uint(d8)});
+}
+
+// lambda B_k / n_bbar
+struct Penalty {
+  float b1, b2, b4, b8;
+};
+__device__ __forceinline__ Penalty penalty(const GradArgs& a) {
+  return Penalty{(float)((double)a.lambda * 1.0 / a.n_bbar), (float)((double)a.lambda * 2.0 / a.n_bbar),
+                 (float)((double)a.lambda * 4.0 / a.n_bbar), (float)((double)a.lambda * 8.0 / a.n_bbar)};
+}
+
+// The logit gradient of group g0 + i from its scales, its sums dv and its pi.
+__device__ __forceinline__ void store_logit_grad(const GradArgs& a, const Penalty& pen, int64_t g0, uint32_t ng, uint32_t i,
+                                                 const Scales& own, const u32x4& dv, const u32x4& pv) {
+  const float a1 = __builtin_fmaf(own.s1, __uint_as_float(dv.x), pen.b1);
+  const float a2 = __builtin_fmaf(own.c2.s, __uint_as_float(dv.y), pen.b2);
+  const float a4 = __builtin_fmaf(own.c4.s, __uint_as_float(dv.z), pen.b4);
+  const float a8 = __builtin_fmaf(own.c8.s, __uint_as_float(dv.w), pen.b8);
+  const float p0 = __uint_as_float(pv.x), p1 = __uint_as_float(pv.y), p2 = __uint_as_float(pv.z), p3 = __uint_as_float(pv.w);
+  const float mean = (p0 * a1 + p1 * a2) + (p2 * a4 + p3 * a8);
+  const u32x4 out = {__float_as_uint(p0 / a.tau * (a1 - mean)), __float_as_uint(p1 / a.tau * (a2 - mean)),
+                     __float_as_uint(p2 / a.tau * (a4 - mean)), __float_as_uint(p3 / a.tau * (a8 - mean))};
+  __builtin_amdgcn_raw_buffer_store_b128(out, rsrc(a.dlogits + g0 * 4, ng * 16u), (int)(i * 16), 0, 0);
+}
+
 // Logit step of Algorithm 1 (section 3.3): with the candidates held constant,
 //   a_k = sum_i G_i w_hat^(B_k)_i + lambda B_k / n,
 //   dL/dl_k = (pi_k / tau) (a_k - sum_j pi_j a_j).
@@ -371,8 +550,7 @@ __global__ __launch_bounds__(64) void vbq_qat_grad_kernel(GradArgs a) {
   const uint32_t base = (uint32_t)(size_t)(__attribute__((address_space(3))) float*)tile;
   const uint32_t cbase = (uint32_t)(size_t)(__attribute__((address_space(3))) float*)consts;
   const TileAddr ta = tile_addr(base, lane);
-  const float pen1 = (float)((double)a.lambda * 1.0 / a.n_bbar), pen2 = (float)((double)a.lambda * 2.0 / a.n_bbar);
-  const float pen4 = (float)((double)a.lambda * 4.0 / a.n_bbar), pen8 = (float)((double)a.lambda * 8.0 / a.n_bbar);
+  const Penalty pen = penalty(a);
   const int64_t stride = gridDim.x;
 
   u32x4 v[16];
@@ -414,55 +592,15 @@ __global__ __launch_bounds__(64) void vbq_qat_grad_kernel(GradArgs a) {
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const uint32_t grp = 4u * j + (lane >> 4);
-      const u32x4 c0 = lds_u32x4(cbase + 32u * grp), c1 = lds_u32x4(cbase + 32u * grp + 16u);
-      Scales sc;
-      sc.s1 = __uint_as_float(c0.x);
-      sc.c2.s = __uint_as_float(c0.y);
-      sc.c4.s = __uint_as_float(c0.z);
-      sc.c8.s = __uint_as_float(c0.w);
-      sc.c2.r = __uint_as_float(c1.x);
-      sc.c4.r = __uint_as_float(c1.y);
-      sc.c8.r = __uint_as_float(c1.z);
-      sc.c2.qmax = 1.0f;
-      sc.c4.qmax = 7.0f;
-      sc.c8.qmax = 127.0f;
-      const u32x4 t = lds_u32x4(ta.co[j]);
-      const float f[4] = {__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w)};
-      const float gr[4] = {__uint_as_float(gv[j].x), __uint_as_float(gv[j].y), __uint_as_float(gv[j].z),
-                           __uint_as_float(gv[j].w)};
-      float d1 = 0.0f, d2 = 0.0f, d4 = 0.0f, d8 = 0.0f;  // sum G q per candidate, this lane's 4 weights
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float q2, q4, q8;
-        levels(f[i], sc, q2, q4, q8);
-        d1 += f[i] >= 0.0f ? gr[i] : -gr[i];  // sign(0) = +1
-        d2 = __builtin_fmaf(gr[i], q2, d2);
-        d4 = __builtin_fmaf(gr[i], q4, d4);
-        d8 = __builtin_fmaf(gr[i], q8, d8);
-      }
-      d1 = row16_sum(d1);
-      d2 = row16_sum(d2);
-      d4 = row16_sum(d4);
-      d8 = row16_sum(d8);
-      // the row's first lane parks the group's sums in the padding of the group's tile row
-      if ((lane & 15u) == 0)
-        lds_store_u32x4(base + 4u * (grp * kRowFloats + 64u),
-                        u32x4{__float_as_uint(d1), __float_as_uint(d2), __float_as_uint(d4), __float_as_uint(d8)});
+      // the sums go to the padding of the group's tile row
+      group_products(lds_u32x4(ta.co[j]), gv[j],
+                     table_scales(lds_u32x4(cbase + 32u * grp), lds_u32x4(cbase + 32u * grp + 16u)),
+                     base + 4u * (grp * kRowFloats + 64u), lane);
     }
     __syncthreads();
 
     // ---- lane per group: the logit gradient of group g0 + lane
-    const u32x4 dv = lds_u32x4(ta.row + 256u);
-    const float a1 = __builtin_fmaf(own.s1, __uint_as_float(dv.x), pen1);
-    const float a2 = __builtin_fmaf(own.c2.s, __uint_as_float(dv.y), pen2);
-    const float a4 = __builtin_fmaf(own.c4.s, __uint_as_float(dv.z), pen4);
-    const float a8 = __builtin_fmaf(own.c8.s, __uint_as_float(dv.w), pen8);
-    const float p0 = __uint_as_float(pv.x), p1 = __uint_as_float(pv.y), p2 = __uint_as_float(pv.z),
-                p3 = __uint_as_float(pv.w);
-    const float mean = (p0 * a1 + p1 * a2) + (p2 * a4 + p3 * a8);
-    const u32x4 out = {__float_as_uint(p0 / a.tau * (a1 - mean)), __float_as_uint(p1 / a.tau * (a2 - mean)),
-                       __float_as_uint(p2 / a.tau * (a4 - mean)), __float_as_uint(p3 / a.tau * (a8 - mean))};
-    __builtin_amdgcn_raw_buffer_store_b128(out, rsrc(a.dlogits + g0 * 4, ng * 16u), (int)(lane * 16), 0, 0);
+    store_logit_grad(a, pen, g0, ng, lane, own, lds_u32x4(ta.row + 256u), pv);
     __syncthreads();  // the next slab overwrites the tile and the table
   };
 
@@ -471,19 +609,59 @@ __global__ __launch_bounds__(64) void vbq_qat_grad_kernel(GradArgs a) {
   for (; slab < a.n_slabs; slab += stride) step(slab);
 }
 
+// The logit step with four waves to a slab (see the narrow forward kernel): 16 groups a wave,
+// weights and gradients in registers in the layout of the loads.
+__global__ __launch_bounds__(kNarrowWaves * 64) void vbq_qat_grad_narrow_kernel(GradArgs a) {
+  __shared__ __attribute__((aligned(16))) float tile[kGroupsPerSlab * kRowFloats];
+  const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  NarrowWave w;
+  w.lane = threadIdx.x & 63u;
+  w.tile = (uint32_t)(size_t)(__attribute__((address_space(3))) float*)tile + wave * (kNarrowGroups * kRowFloats * 4u);
+  for (int64_t slab = blockIdx.x; slab < a.n_slabs; slab += gridDim.x) {
+    narrow_slab(w, slab, a.n_groups, wave);
+    const uint32_t lane = w.lane, grp = lane & 15u;
+    u32x4 v[kNarrowLoads], gv[kNarrowLoads];
+    narrow_load(w, a.W, v);
+    narrow_load(w, a.grad, gv);
+    const u32x4 pv = __builtin_amdgcn_raw_buffer_load_b128(rsrc(a.pi + w.g0 * 4, w.ng * 16u), (int)(grp * 16), 0, 0);
+    const Scales own = narrow_scales(w, v);
+    const uint32_t own_row = w.tile + 4u * grp * kRowFloats;
+    wave_phase();
+    lds_store_u32x4(own_row, u32x4{__float_as_uint(own.s1), __float_as_uint(own.c2.s),
+                                               __float_as_uint(own.c4.s), __float_as_uint(own.c8.s)});
+    lds_store_u32x4(own_row + 16u, u32x4{__float_as_uint(own.c2.r), __float_as_uint(own.c4.r),
+                                                     __float_as_uint(own.c8.r), 0u});
+    wave_phase();
+#pragma unroll
+    for (int j = 0; j < kNarrowLoads; ++j) {
+      const uint32_t row = w.tile + 4u * (4u * j + (lane >> 4)) * kRowFloats;
+      group_products(v[j], gv[j], table_scales(lds_u32x4(row), lds_u32x4(row + 16u)), row + 32u, lane);
+    }
+    wave_phase();
+    if (lane < w.ng) store_logit_grad(a, penalty(a), w.g0, w.ng, lane, own, lds_u32x4(own_row + 32u), pv);
+    wave_phase();
+  }
+}
+
 // bbar = (sum of the per-block sums) / n_groups, summed in a fixed order.
 __global__ __launch_bounds__(kBbarThreads) void vbq_qat_bbar_kernel(const double* partial, int n, double n_groups,
                                                                     double* bbar) {
-  __shared__ double red[kBbarThreads];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += kBbarThreads) s += partial[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int h = kBbarThreads / 2; h >= 1; h >>= 1) {
-    if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-    __syncthreads();
+  __shared__ double red[kBbarThreads / 64];
+  // every load goes out before the first is added (one memory latency)
+  double v[kMaxBlocks / kBbarThreads];
+#pragma unroll
+  for (int k = 0; k < kMaxBlocks / kBbarThreads; ++k) {
+    const int i = (int)threadIdx.x + k * kBbarThreads;
+    v[k] = partial[i < n ? i : 0];
   }
-  if (threadIdx.x == 0) *bbar = red[0] / n_groups;
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < kMaxBlocks / kBbarThreads; ++k) s += (int)threadIdx.x + k * kBbarThreads < n ? v[k] : 0.0;
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) *bbar = ((red[0] + red[1]) + (red[2] + red[3])) / n_groups;
 }
 
 int64_t qat_blocks(int64_t n_groups) {
@@ -535,9 +713,12 @@ vbq_status vbq_qat_forward(int64_t n_groups, const float* W_dev, const float* lo
   a.n_groups = n_groups;
   a.n_slabs = (n_groups + kGroupsPerSlab - 1) / kGroupsPerSlab;
   void* args[] = {&a};
-  const void* kernel = (flags & VBQ_QAT_WSOFT_BF16) ? (const void*)vbq_qat_forward_kernel<true>
-                                                    : (const void*)vbq_qat_forward_kernel<false>;
-  vbq_status st = vbq_detail_hip_status(hipLaunchKernel(kernel, dim3((unsigned)blocks), dim3(64), args, 0, s));
+  const bool bf16 = (flags & VBQ_QAT_WSOFT_BF16) != 0, narrow = !bf16 || a.n_slabs <= kNarrowBf16Slabs;
+  const void* kernel = !narrow ? (const void*)vbq_qat_forward_kernel
+                       : bf16  ? (const void*)vbq_qat_forward_narrow_kernel<true>
+                               : (const void*)vbq_qat_forward_narrow_kernel<false>;
+  vbq_status st = vbq_detail_hip_status(
+      hipLaunchKernel(kernel, dim3((unsigned)blocks), dim3(narrow ? kNarrowWaves * 64 : 64), args, 0, s));
   if (st != VBQ_OK || !bbar_dev) return st;
   const double* part = (const double*)workspace_dev;
   int n = (int)blocks;
@@ -569,9 +750,11 @@ vbq_status vbq_qat_logit_grad(int64_t n_groups, const float* W_dev, const float*
   a.n_groups = n_groups;
   a.n_slabs = (n_groups + kGroupsPerSlab - 1) / kGroupsPerSlab;
   void* args[] = {&a};
-  const int64_t blocks = a.n_slabs < kGradBlocks ? a.n_slabs : kGradBlocks;
-  return vbq_detail_hip_status(hipLaunchKernel((const void*)vbq_qat_grad_kernel, dim3((unsigned)blocks), dim3(64),
-                                               args, 0, (hipStream_t)stream));
+  const bool narrow = a.n_slabs <= kNarrowGradSlabs;
+  const int64_t most = narrow ? kNarrowGradBlocks : kGradBlocks, blocks = a.n_slabs < most ? a.n_slabs : most;
+  return vbq_detail_hip_status(hipLaunchKernel(narrow ? (const void*)vbq_qat_grad_narrow_kernel : (const void*)vbq_qat_grad_kernel,
+                                               dim3((unsigned)blocks), dim3(narrow ? kNarrowWaves * 64 : 64), args, 0,
+                                               (hipStream_t)stream));
 }
 
 }  // extern "C"

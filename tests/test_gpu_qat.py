@@ -442,3 +442,30 @@ def test_tiny_tau_is_one_hot_on_the_noisy_argmax(vbq, tau):
     cand = oqat.candidates(W.reshape(n, 64).astype(np.float64)).reshape(4, n, 64)
     assert np.array_equal(w_soft.reshape(n, 64).astype(np.float64), cand[k, np.arange(n)])
     assert float(bbar[0]) == pytest.approx(WIDTHS[k].mean(), rel=1e-12)
+
+
+# a slab (64 groups) goes to four waves or to one by the number of slabs: the
+# same groups on both sides of each rule give the same bits
+@pytest.mark.parametrize("over", [1, 65])
+def test_bf16_forward_on_both_sides_of_the_slab_rule(vbq, over):
+    n = 64 * 8192
+    _say(f"qat bf16 forward {n} and {n + over} groups")
+    W, logits, noise = (_dev(a) for a in synth.selection_inputs(n + over, part=31))
+    few = vbq.qat_forward(W[:64 * n], logits[:n], noise[:n], 0.5, w_soft_dtype=torch.bfloat16)
+    many = vbq.qat_forward(W, logits, noise, 0.5, w_soft_dtype=torch.bfloat16)
+    f32 = vbq.qat_forward(W, logits, noise, 0.5)
+    for a, b, c in zip(few[:3], many[:3], f32[:3]):
+        assert torch.equal(a, b[:a.numel() // (4 if a.dim() == 2 else 1)])
+        assert torch.equal(b, c.to(b.dtype))
+
+
+@pytest.mark.parametrize("over", [1, 65])
+def test_logit_grad_on_both_sides_of_the_slab_rule(vbq, over):
+    n = 64 * 16384
+    _say(f"qat logit grad {n} and {n + over} groups")
+    W, logits, _ = (_dev(a) for a in synth.selection_inputs(n + over, part=37))
+    G = torch.randn(64 * (n + over), device="cuda", generator=torch.Generator(device="cuda").manual_seed(5))
+    pi = torch.softmax(logits, dim=1)
+    few = vbq.qat_logit_grad(W[:64 * n], G[:64 * n], pi[:n], 0.5, 0.1, n_bbar=n)
+    many = vbq.qat_logit_grad(W, G, pi, 0.5, 0.1, n_bbar=n)
+    assert torch.equal(few, many[:n])
