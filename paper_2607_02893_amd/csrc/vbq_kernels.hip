@@ -56,13 +56,18 @@ struct DevMatrix {
   int32_t N, K, G, R, C, T, U, logR;
 };
 
+// The address space is spelled out for pointers that a kernel reads from memory
+// (the step's plan): the compiler would use flat accesses for them, which count
+// as LDS accesses too, so every wait for an LDS read would also wait for all the
+// code loads in flight.
+#define VBQ_GLOBAL __attribute__((address_space(1)))
 template <typename T>
 __device__ __forceinline__ T ld(const uint8_t* base, uint32_t off) {
-  return *(const T*)(base + off);
+  return *(const VBQ_GLOBAL T*)((const VBQ_GLOBAL uint8_t*)base + off);
 }
 template <typename T>
 __device__ __forceinline__ T ld_nt(const uint8_t* base, uint32_t off) {
-  return __builtin_nontemporal_load((const T*)(base + off));
+  return __builtin_nontemporal_load((const VBQ_GLOBAL T*)((const VBQ_GLOBAL uint8_t*)base + off));
 }
 
 struct MvArgs {
@@ -2513,10 +2518,10 @@ __device__ __forceinline__ void load_x1_coherent(const uint16_t* x, int K, int j
 
 __device__ __forceinline__ void store_y_coherent(void* y, size_t i, float v, int32_t f16) {
   if (f16)
-    __hip_atomic_store((uint16_t*)y + i, __builtin_bit_cast(uint16_t, (_Float16)v), __ATOMIC_RELAXED,
+    __hip_atomic_store((VBQ_GLOBAL uint16_t*)y + i, __builtin_bit_cast(uint16_t, (_Float16)v), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
   else
-    __hip_atomic_store((float*)y + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store((VBQ_GLOBAL float*)y + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Waits until GEMV `op` has n_wg arrivals (wave 0 polls the eight words,
@@ -2676,7 +2681,7 @@ __global__ __launch_bounds__(kStepWaves * 64) void vbq_step_kernel(const StepOp*
           if (o->rows == nullptr) {
             store_y_coherent(o->y, row, tot, o->yf16);
           } else {
-            const int64_t d = o->rows[row];
+            const int64_t d = ld<int32_t>((const uint8_t*)o->rows, 4u * (uint32_t)row);
             if (d >= 0 && d < o->ylen) store_y_coherent(o->y, (size_t)d, tot, o->yf16);
           }
         }
