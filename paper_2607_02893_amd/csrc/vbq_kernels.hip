@@ -76,7 +76,7 @@ struct MvArgs {
   void* y;            // row m at y + m*ldy elements (float, or fp16 bits when yf16)
   int64_t ldx, ldy;
   int32_t M;          // rows of x actually present (<= MT)
-  int32_t S;          // slices per unit
+  int32_t lgS;        // log2 of the slices per unit
   int32_t SW;         // group columns per window (LDS staging)
   int32_t yf16;       // 1: y holds fp16 (each fp32 result rounded to nearest even)
   // one activation row only: output row n goes to y[rows[n]] (skipped unless
@@ -317,19 +317,29 @@ __host__ __device__ inline int mv_lds_bytes(int R, int SW, int MT, int NW, int t
 // Group columns per width-map word (1 when a column spans whole words).
 __host__ __device__ inline int cols_per_word(int R) { return R >= 64 ? 1 : 64 / R; }
 
-// Columns [cb, ce) of slice s of S of a unit with `cols` columns.
-__host__ __device__ inline void slice_cols(int cols, int R, int s, int S, int& cb, int& ce) {
-  const int cw = cols_per_word(R);
-  const int per = ((cols + cw - 1) / cw + S - 1) / S;
-  cb = min(cols, s * per * cw);
-  ce = min(cols, (s + 1) * per * cw);
+// Columns [cb, ce) of slice s of 2^lgS of a unit with `cols` columns.  (Slice
+// counts are powers of two: a division by a value known only at run time is
+// some 30 instructions, at 2 ns each in a wave that has its SIMD to itself.)
+__host__ __device__ inline void slice_cols(int cols, int logR, int s, int lgS, int& cb, int& ce) {
+  const int lcw = logR >= 6 ? 0 : 6 - logR;  // log2 of the columns per width-map word
+  const int words = (cols + (1 << lcw) - 1) >> lcw;
+  const int per = (words + (1 << lgS) - 1) >> lgS;
+  cb = min(cols, (s * per) << lcw);
+  ce = min(cols, ((s + 1) * per) << lcw);
 }
 
 // Columns of the widest slice of a unit of C columns.
-__host__ __device__ inline int max_slice_cols(int R, int C, int S) {
+__host__ __device__ inline int max_slice_cols(int logR, int C, int lgS) {
   int cb, ce;
-  slice_cols(C, R, 0, S, cb, ce);
+  slice_cols(C, logR, 0, lgS, cb, ce);
   return ce - cb;
+}
+
+// The smallest power of two (as its logarithm) with at least n.
+inline int log2_up(int64_t n) {
+  int l = 0;
+  while (((int64_t)1 << l) < n) ++l;
+  return l;
 }
 
 __device__ __forceinline__ u32x4 lds_u32x4(uint32_t addr) {
@@ -962,7 +972,7 @@ __device__ __forceinline__ int clamp_run(const DevMatrix& mat, int c, uint32_t s
 // unit's first entry follows from the geometry.  Shared by vbq_mv_kernel and
 // the all-buckets kernel.
 template <int NW, int UNI>
-__device__ __forceinline__ void uniform_tile(const DevMatrix& mat, const MvArgs& a, int t, int S, int SW) {
+__device__ __forceinline__ void uniform_tile(const DevMatrix& mat, const MvArgs& a, int t, int lgS, int SW) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int R = mat.R;
   const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)smem;
@@ -982,12 +992,12 @@ __device__ __forceinline__ void uniform_tile(const DevMatrix& mat, const MvArgs&
   wn.logR = mat.logR;
   for (int i = (int)lane; i < R; i += 64) lds_store_f32(ysum + 4u * i, 0.0f);
 
-  for (int item = wave; item < mat.U * S; item += NW) {
+  for (int item = wave; item < (mat.U << lgS); item += NW) {
     const uint32_t lane = lane_id_here();
-    const int k = item / S, sl = item - k * S;
+    const int k = item >> lgS, sl = item & ((1 << lgS) - 1);
     const UnitInfo u = load_unit(mat, t, k);
     int cb, ce;
-    slice_cols(u.cols, R, sl, S, cb, ce);
+    slice_cols(u.cols, mat.logR, sl, lgS, cb, ce);
     if (cb >= ce) continue;  // wave-uniform: an empty slice
     XRegs xr;
     load_x1(a.x, u.j0 + cb, ce - cb, xr, lane);
@@ -1045,7 +1055,7 @@ __device__ __forceinline__ void uniform_tile(const DevMatrix& mat, const MvArgs&
 // The values the first memory accesses depend on come as separate leading
 // arguments, which the command processor can place in SGPRs before the wave
 // starts (kernel-argument preloading), so the first loads do not wait for a
-// kernel-argument fetch.  geo packs R (9 bits), C (8), log2 R (4) and S (8);
+// kernel-argument fetch.  geo packs R (9 bits), C (8), log2 R (4) and log2 S (8);
 // sw_m packs SW (16) and M (16).  (At most 16 SGPRs can be preloaded, two
 // of which hold the kernel-argument pointer: these eleven take 13.)
 //
@@ -1083,10 +1093,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(MT == 1
   mat.logR = (int)((geo >> 17) & 0xF);
   a.x = x;
   a.M = (int)(sw_m >> 16);
-  const int R = mat.R, SW = (int)(sw_m & 0xFFFF), S = (int)(geo >> 21);
+  const int R = mat.R, SW = (int)(sw_m & 0xFFFF), lgS = (int)(geo >> 21);
   if constexpr (UNI >= 0) {
     static_assert(MT == 1, "one-width matrices take one activation row");
-    uniform_tile<NW, UNI>(mat, a, blockIdx.x, S, SW);  // one row tile per workgroup
+    uniform_tile<NW, UNI>(mat, a, blockIdx.x, lgS, SW);  // one row tile per workgroup
   } else {
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)smem;
     const uint32_t lane = lane_id();
@@ -1108,13 +1118,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(MT == 1
     const uint32_t inv = region + P.inv;
     for (int i = (int)lane; i < NS; i += 64) lds_store_f32(ysum + 4u * i, 0.0f);
 
-    for (int item = wave; item < mat.U * S; item += NW) {
+    for (int item = wave; item < (mat.U << lgS); item += NW) {
       const uint32_t lane = lane_id_here();
-      const int k = item / S, sl = item - k * S;
+      const int k = item >> lgS, sl = item & ((1 << lgS) - 1);
       const UnitInfo u = load_unit(mat, t, k);
       const int unit = t * mat.U + k;
       int cb, ce;
-      slice_cols(u.cols, R, sl, S, cb, ce);
+      slice_cols(u.cols, mat.logR, sl, lgS, cb, ce);
       if (cb >= ce) continue;  // wave-uniform: an empty slice
       // one or two rows: a wave's set-up (x, the map, the first code loads and
       // the index) runs at a raised issue priority, so a wave that has just
@@ -1128,7 +1138,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(MT == 1
       // A whole-unit item (one slice per unit) reads where its class runs start
       // and how long they are from the unit table (rows u and u + 1): no class
       // counts, and its code loads do not wait for the width map.
-      const bool whole = MT == 1 && S == 1;  // wave-uniform
+      const bool whole = MT == 1 && lgS == 0;  // wave-uniform
       const u32x16 rows2 = unit_rows(mat, unit);
       const u32x4 erow = rows2.s0123, enext = rows2.s89ab;
       const uint32_t ustart[4] = {erow.x, erow.y, erow.z, erow.w};
@@ -1234,7 +1244,7 @@ struct BucketsArgs {
   const int32_t* rows[VBQ_MAX_BUCKETS];  // output row of each bucket row
   int32_t tile0[VBQ_MAX_BUCKETS];        // first workgroup of each bucket
   int32_t cls[VBQ_MAX_BUCKETS];          // width class (log2 bits)
-  int32_t S[VBQ_MAX_BUCKETS];            // slices per unit
+  int32_t lgS[VBQ_MAX_BUCKETS];          // log2 of the slices per unit
   int32_t SW[VBQ_MAX_BUCKETS];           // window columns
   int32_t n;                             // buckets
   int32_t yf16;
@@ -1256,17 +1266,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
   a.ldx = 0;
   a.ldy = 0;
   a.M = 1;
-  a.S = ba.S[b];
+  a.lgS = ba.lgS[b];
   a.SW = ba.SW[b];
   a.yf16 = ba.yf16;
   a.rows = ba.rows[b];
   a.ylen = ba.ylen;
   const int t = (int)blockIdx.x - ba.tile0[b];
   switch (ba.cls[b]) {
-    case 0: uniform_tile<NW, 0>(a.m, a, t, a.S, a.SW); break;
-    case 1: uniform_tile<NW, 1>(a.m, a, t, a.S, a.SW); break;
-    case 2: uniform_tile<NW, 2>(a.m, a, t, a.S, a.SW); break;
-    default: uniform_tile<NW, 3>(a.m, a, t, a.S, a.SW); break;
+    case 0: uniform_tile<NW, 0>(a.m, a, t, a.lgS, a.SW); break;
+    case 1: uniform_tile<NW, 1>(a.m, a, t, a.lgS, a.SW); break;
+    case 2: uniform_tile<NW, 2>(a.m, a, t, a.lgS, a.SW); break;
+    default: uniform_tile<NW, 3>(a.m, a, t, a.lgS, a.SW); break;
   }
 }
 
@@ -1573,7 +1583,7 @@ struct MmArgs {
   void* y;            // row m at y + m*ldy elements (float, or fp16 bits when yf16)
   int64_t ldx, ldy;
   int32_t M;          // rows of X (1..16)
-  int32_t S;          // slices per unit
+  int32_t lgS;        // log2 of the slices per unit
   int32_t yf16;       // 1: y holds fp16
 };
 
@@ -1830,7 +1840,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 1
   mat.R = (int)(geo & 0x1FF);
   mat.C = (int)((geo >> 9) & 0xFF);
   mat.logR = (int)((geo >> 17) & 0xF);
-  const int R = mat.R, S = (int)(geo >> 21);
+  const int R = mat.R, lgS = (int)(geo >> 21);
   const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)smem;
   const int wave = wave_id();
   const int t = blockIdx.x;  // one row tile per workgroup
@@ -1844,12 +1854,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 1
     float4_t acc[RB];
 #pragma unroll
     for (int i = 0; i < RB; ++i) acc[i] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int item = wave; item < mat.U * S; item += NW) {
-      const int k = item / S, sl = item - k * S;
+    for (int item = wave; item < (mat.U << lgS); item += NW) {
+      const int k = item >> lgS, sl = item & ((1 << lgS) - 1);
       const UnitInfo u = load_unit(mat, t, k);
       const int unit = t * mat.U + k;
       int cb, ce;
-      slice_cols(u.cols, R, sl, S, cb, ce);
+      slice_cols(u.cols, mat.logR, sl, lgS, cb, ce);
       if (cb >= ce) continue;  // wave-uniform: an empty slice
       const int wb = (cb * R) >> 6, we = (ce * R + 63) >> 6;
       // The words of one range, the next one in flight while one is multiplied.
@@ -1948,7 +1958,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 1
 constexpr int kDequantWaves = 4;
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // W may be only 4-byte aligned
 
-__global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatrix mat, float* W, int S) {
+__global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatrix mat, float* W, int lgS) {
   __shared__ __attribute__((aligned(16))) uint32_t hand_s[kDequantWaves * 128];  // per position: codes and class, scale
   const uint32_t lane = lane_id();
   const int wave = wave_id();
@@ -1956,10 +1966,10 @@ __global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatr
   const uint32_t hand = (uint32_t)(size_t)(__attribute__((address_space(3))) uint32_t*)hand_s + 512u * (uint32_t)wave;
   const uint32_t grp = lane >> 4, sub = lane & 15u;
   const uint32_t mine = hand + 128u * grp;
-  for (int item = wave; item < mat.U * S; item += kDequantWaves) {
-    const int k = item / S, sl = item - k * S;
+  for (int item = wave; item < (mat.U << lgS); item += kDequantWaves) {
+    const int k = item >> lgS, sl = item & ((1 << lgS) - 1);
     const UnitInfo u = load_unit(mat, t, k);
-    const int per = (u.W + S - 1) / S;
+    const int per = (u.W + (1 << lgS) - 1) >> lgS;
     const int wb = min(u.W, sl * per), we = min(u.W, wb + per);
     if (wb >= we) continue;
     const int unit = t * mat.U + k;
@@ -2069,7 +2079,7 @@ constexpr int kMinWaves = 4;
 // Launch shape of the fused product for MT activation rows.
 struct MvShape {
   int NW;  // waves per workgroup (4, 8 or 16)
-  int S;   // slices per unit
+  int lgS; // log2 of the slices per unit
   int SW;  // window columns
   int lds; // dynamic LDS bytes
 };
@@ -2083,14 +2093,14 @@ struct MvShape {
 // of a CU), else the largest multiple of the columns per width-map word
 // that does.
 bool choose_shape(const DevMatrix& m, int MT, MvShape* sh) {
-  int S = (kMinWaves + m.U - 1) / m.U;
+  int lgS = log2_up((kMinWaves + m.U - 1) / m.U);
   if (MT == 1)
-    while (max_slice_cols(m.R, m.C, S) > kXRegs * 8) ++S;
+    while (max_slice_cols(m.logR, m.C, lgS) > kXRegs * 8) ++lgS;
   const int max_nw = MT == 1 ? 16 : 8;  // several rows need more than 128 VGPRs: 2 waves per SIMD
   int NW = kMinWaves;
-  while (NW < max_nw && NW < m.U * S) NW *= 2;
+  while (NW < max_nw && NW < (m.U << lgS)) NW *= 2;
   const int cw = cols_per_word(m.R);
-  const int full = max_slice_cols(m.R, m.C, S);
+  const int full = max_slice_cols(m.logR, m.C, lgS);
   int SW = 0;
   if (MT == 1) {
     if (mv_lds_bytes(m.R, full, 1, NW) <= kLdsLimit) SW = full;
@@ -2107,7 +2117,7 @@ bool choose_shape(const DevMatrix& m, int MT, MvShape* sh) {
   }
   if (SW <= 0) return false;
   sh->NW = NW;
-  sh->S = S;
+  sh->lgS = lgS;
   sh->SW = SW;
   sh->lds = mv_lds_bytes(m.R, SW, MT, NW);
   return true;
@@ -2155,7 +2165,7 @@ vbq_status launch_mv_nw(const MvArgs& a, int lds, hipStream_t s) {
   }
   uint32_t wmap_words = a.m.wmap_words;
   int32_t G = a.m.G, N = a.m.N, U = a.m.U;
-  uint32_t geo = (uint32_t)a.m.R | ((uint32_t)a.m.C << 9) | ((uint32_t)a.m.logR << 17) | ((uint32_t)a.S << 21);
+  uint32_t geo = (uint32_t)a.m.R | ((uint32_t)a.m.C << 9) | ((uint32_t)a.m.logR << 17) | ((uint32_t)a.lgS << 21);
   uint32_t sw_m = (uint32_t)a.SW | ((uint32_t)a.M << 16);
   void* kargs[] = {&x, &blob, &off_wmap, &tile_words, &chunk_words, &wmap_words, &G, &N, &geo, &U, &sw_m, &args};
   return hip_status(hipLaunchKernel(kernel, dim3((unsigned)a.m.T), dim3(NW * 64), kargs, (size_t)lds, s));
@@ -2180,7 +2190,7 @@ vbq_status launch_pair_nw(const MvArgs& a, int lds, hipStream_t s) {
   uint32_t off_wmap = a.m.off_wmap, tile_words = a.m.tile_words, chunk_words = a.m.chunk_words;
   uint32_t wmap_words = a.m.wmap_words;
   int32_t G = a.m.G, N = a.m.N, U = a.m.U;
-  uint32_t geo = (uint32_t)a.m.R | ((uint32_t)a.m.C << 9) | ((uint32_t)a.m.logR << 17) | (1u << 21);
+  uint32_t geo = (uint32_t)a.m.R | ((uint32_t)a.m.C << 9) | ((uint32_t)a.m.logR << 17);
   uint32_t sw_m = (uint32_t)a.SW | ((uint32_t)a.M << 16);
   void* kargs[] = {&x, &blob, &off_wmap, &tile_words, &chunk_words, &wmap_words, &G, &N, &geo, &U, &sw_m, &args};
   return hip_status(hipLaunchKernel(kernel, dim3((unsigned)a.m.T), dim3(NW * 64), kargs, (size_t)lds, s));
@@ -2216,7 +2226,7 @@ vbq_status try_launch_pair(const DevMatrix& m, const void* x, int64_t ldx, void*
   a.ldx = ldx;
   a.ldy = ldy;
   a.M = MT;
-  a.S = 1;
+  a.lgS = 0;
   a.SW = m.C;
   a.yf16 = yf16 ? 1 : 0;
   a.rows = MT == 1 ? rows : nullptr;
@@ -2248,7 +2258,7 @@ vbq_status launch_mv(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
   a.ldx = ldx;
   a.ldy = ldy;
   a.M = M;
-  a.S = sh.S;
+  a.lgS = sh.lgS;
   a.SW = sh.SW;
   a.yf16 = yf16 ? 1 : 0;
   a.rows = MT == 1 ? rows : nullptr;
@@ -2304,7 +2314,7 @@ vbq_status launch_mm_nw(const MmArgs& a, int lds, hipStream_t s) {
   }
   uint32_t wmap_words = a.m.wmap_words;
   int32_t G = a.m.G, N = a.m.N, U = a.m.U, M = a.M;
-  uint32_t geo = (uint32_t)a.m.R | ((uint32_t)a.m.C << 9) | ((uint32_t)a.m.logR << 17) | ((uint32_t)a.S << 21);
+  uint32_t geo = (uint32_t)a.m.R | ((uint32_t)a.m.C << 9) | ((uint32_t)a.m.logR << 17) | ((uint32_t)a.lgS << 21);
   void* kargs[] = {&blob, &off_wmap, &tile_words, &chunk_words, &wmap_words, &G, &N, &geo, &U, &M, &args};
   return hip_status(hipLaunchKernel(kernel, dim3((unsigned)a.m.T), dim3(NW * 64), kargs, (size_t)lds, s));
 }
@@ -2332,24 +2342,24 @@ vbq_status launch_mm_uni(const MmArgs& a, int uni, int NW, int lds, hipStream_t 
 // workgroup leave a wave 128 registers: 2048 x 2048 M = 4 took 8.1 us against
 // 4.3), as long as the whole grid fits the GPU at once (about 20 waves per CU
 // at this kernel's register use).
-bool mm_shape(const DevMatrix& m, int M, int* NWo, int* So, int* ldso) {
+bool mm_shape(const DevMatrix& m, int M, int* NWo, int* lgSo, int* ldso) {
   int NWt = kMinWaves;
   while (NWt < 8 && (int64_t)m.T * NWt * 2 <= 256 * 20) NWt *= 2;
-  int S = (NWt + m.U - 1) / m.U;
-  while (max_slice_cols(m.R, m.C, S) > kMmMaxCols) ++S;
+  int lgS = log2_up((NWt + m.U - 1) / m.U);
+  while (max_slice_cols(m.logR, m.C, lgS) > kMmMaxCols) ++lgS;
   const int wbytes = mm_wave_bytes(m.R, M);
   int NW = kMinWaves;  // (fewer waves than items is fine: items are dealt in turn)
-  while (NW < 8 && NW < m.U * S && 2 * NW * wbytes <= kLdsLimit) NW *= 2;
+  while (NW < 8 && NW < (m.U << lgS) && 2 * NW * wbytes <= kLdsLimit) NW *= 2;
   *NWo = NW;
-  *So = S;
+  *lgSo = lgS;
   *ldso = NW * wbytes;
   return NW * wbytes <= kLdsLimit;
 }
 
 vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t ldx, int M, void* y, int64_t ldy,
                      hipStream_t s) {
-  int NW, S, lds;
-  if (!mm_shape(m, M, &NW, &S, &lds)) return VBQ_ERR_UNSUPPORTED;
+  int NW, lgS, lds;
+  if (!mm_shape(m, M, &NW, &lgS, &lds)) return VBQ_ERR_UNSUPPORTED;
   MmArgs a;
   a.m = m;
   a.x = (const uint16_t*)x;
@@ -2357,7 +2367,7 @@ vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
   a.ldx = ldx;
   a.ldy = ldy;
   a.M = M;
-  a.S = S;
+  a.lgS = lgS;
   a.yf16 = (flags & VBQ_Y_F16) ? 1 : 0;
   // row blocks of 16 per group: one, two or four (R = 16, 32, >= 64)
   const int uni = one_class(m);
@@ -2406,7 +2416,7 @@ bool plan_buckets(const vbq_bucket* bk, int n, const void* blob, const int32_t* 
     ba->rows[k] = rows + bk[i].row_begin;
     ba->tile0[k] = tiles;
     ba->cls[k] = uni;
-    ba->S[k] = sh.S;
+    ba->lgS[k] = sh.lgS;
     ba->SW[k] = sh.SW;
     if ((int64_t)tiles + m.T > INT32_MAX) return false;
     tiles += (int)m.T;
@@ -2448,8 +2458,8 @@ const char* kernel_name(const DevMatrix& m, uint32_t flags, int M) {
     if (M == 2) return sh.NW == 4 ? "vbq_mv_kernel<2,4>" : "vbq_mv_kernel<2,8>";
     return kMv[c][sh.NW == 4 ? 0 : sh.NW == 8 ? 1 : 2];
   }
-  int NW, S, lds;
-  if (!mm_shape(m, M, &NW, &S, &lds)) return "none";
+  int NW, lgS, lds;
+  if (!mm_shape(m, M, &NW, &lgS, &lds)) return "none";
   return kMm[m.R == 16 ? 0 : m.R == 32 ? 1 : 2][c][NW == 4 ? 0 : 1];
 }
 
@@ -2564,9 +2574,9 @@ __global__ __launch_bounds__(kStepWaves * 64) void vbq_step_kernel(const StepOp*
     const StepOp* o = plan + op;
     DevMatrix mat = o->m;
     const int R = mat.R, U = mat.U, T = mat.T;
-    const int tpr = U <= kStepPairs / 2 ? 2 : 1;  // tiles per round
-    const int ups = kStepPairs / tpr;              // unit slots per tile
-    const int slot = pair / ups, k = pair % ups;
+    const int two = U <= kStepPairs / 2 ? 1 : 0;  // tiles per round: two or one
+    const int tpr = 1 << two, ups = kStepPairs >> two;  // (unit slots per tile)
+    const int slot = two ? pair >> 2 : 0, k = pair & (ups - 1);
     const WavePlan P = wave_plan(R, mat.C, 1);
     const uint32_t ysum0 = base;  // pair p's unit row sums at ysum0 + p*R*4
     const uint32_t ysum = ysum0 + (uint32_t)(pair * R * 4);
@@ -2580,13 +2590,10 @@ __global__ __launch_bounds__(kStepWaves * 64) void vbq_step_kernel(const StepOp*
     wn.SW = mat.C;
     wn.logR = mat.logR;
     const uint32_t inv = region + P.inv;
-    const int my_tiles = wg < T ? (T - wg + n_wg - 1) / n_wg : 0;
-    const int rounds = (my_tiles + tpr - 1) / tpr;
-    for (int rd = 0; rd < rounds; ++rd) {
+    for (int rd = 0; wg + (rd << two) * n_wg < T; ++rd) {
       const uint32_t lane = lane_id_here();  // (values derived from it are not hoisted out of the loops)
-      const int ti = rd * tpr + slot;
-      const int t = wg + ti * n_wg;
-      const bool active = ti < my_tiles && k < U;  // wave-uniform
+      const int t = wg + ((rd << two) + slot) * n_wg;
+      const bool active = t < T && k < U;  // wave-uniform
       const bool must_wait = rd == 0 && op > 0;    // workgroup-uniform
       const UnitInfo u = load_unit(mat, active ? t : 0, active ? k : 0);
       const int unit = (active ? t : 0) * mat.U + (active ? k : 0);
@@ -2672,9 +2679,9 @@ __global__ __launch_bounds__(kStepWaves * 64) void vbq_step_kernel(const StepOp*
       }
       // per tile slot: the unit row sums added in unit order, stored coherently
       for (int i = threadIdx.x; i < tpr * R; i += kStepWaves * 64) {
-        const int sl = i / R, r = i - sl * R;
-        const int tt = wg + (rd * tpr + sl) * n_wg;
-        if (live && rd * tpr + sl < my_tiles && r < min(R, mat.N - tt * R)) {
+        const int sl = i >> mat.logR, r = i & (R - 1);
+        const int tt = wg + ((rd << two) + sl) * n_wg;
+        if (live && tt < T && r < min(R, mat.N - tt * R)) {
           float tot = 0.0f;
           for (int kk = 0; kk < U; ++kk) tot += lds_f32(ysum0 + 4u * (uint32_t)((sl * ups + kk) * R + r));
           const size_t row = (size_t)tt * R + r;
@@ -2867,8 +2874,9 @@ vbq_status vbq_dequant(const vbq_desc* desc, const void* blob_dev, float* W_dev,
   // from the stores and loads in flight), a word at least each
   const int64_t units = (int64_t)m.T * m.U;
   const int unit_words = (int)(((int64_t)m.C * m.R + 63) / 64);
-  int S = (int)std::min<int64_t>(std::max<int64_t>((8192 + units - 1) / units, (kDequantWaves + m.U - 1) / m.U), unit_words);
-  void* args[] = {&m, &W_dev, &S};
+  int lgS = std::min(log2_up(std::max<int64_t>((8192 + units - 1) / units, (kDequantWaves + m.U - 1) / m.U)),
+                     log2_up(unit_words));
+  void* args[] = {&m, &W_dev, &lgS};
   return hip_status(hipLaunchKernel((const void*)vbq_dequant_kernel, dim3((unsigned)m.T), dim3(kDequantWaves * 64), args, 0,
                                     (hipStream_t)stream));
 }
