@@ -384,15 +384,17 @@ struct WmapRegs {
   uint64_t b0, b1;  // plane 0 / plane 1 of word l + 64
 };
 
-__device__ __forceinline__ WmapRegs load_wmap(const DevMatrix& mat, const UnitInfo& u, int we, uint32_t lane) {
+__device__ __forceinline__ void load_wmap64(const DevMatrix& mat, const UnitInfo& u, int we, uint32_t l, uint64_t& p0,
+                                            uint64_t& p1) {
   const uint32_t last = mat.wmap_words - 1;
-  const uint32_t top = (uint32_t)(max(we, 1) - 1);
-  const uint32_t wa = min(lane, top), wb = min(lane + 64u, top);
+  const uint32_t w = min(l, (uint32_t)(max(we, 1) - 1));
+  p0 = ld<uint64_t>(mat.blob, mat.off_wmap + 8u * min(u.wmap_word + w, last));
+  p1 = ld<uint64_t>(mat.blob, mat.off_wmap + 8u * min(u.wmap_word + (uint32_t)u.W + w, last));
+}
+__device__ __forceinline__ WmapRegs load_wmap(const DevMatrix& mat, const UnitInfo& u, int we, uint32_t lane) {
   WmapRegs r;
-  r.a0 = ld<uint64_t>(mat.blob, mat.off_wmap + 8u * min(u.wmap_word + wa, last));
-  r.a1 = ld<uint64_t>(mat.blob, mat.off_wmap + 8u * min(u.wmap_word + (uint32_t)u.W + wa, last));
-  r.b0 = ld<uint64_t>(mat.blob, mat.off_wmap + 8u * min(u.wmap_word + wb, last));
-  r.b1 = ld<uint64_t>(mat.blob, mat.off_wmap + 8u * min(u.wmap_word + (uint32_t)u.W + wb, last));
+  load_wmap64(mat, u, we, lane, r.a0, r.a1);
+  load_wmap64(mat, u, we, lane + 64u, r.b0, r.b1);
   return r;
 }
 
@@ -477,9 +479,7 @@ __device__ __forceinline__ WinCounts window_counts(const WmapRegs& wr, const Uni
 // conditions), and real positions write their slot.  No branch depends on
 // the data.  Words whose 64 positions are all real (every word but a unit's
 // last one, outside the ragged last tile) skip the validity masks.
-// kFwd: write the other direction instead, fwd[pos] = (class << 14) | rank of
-// the position inside its class (run[] then starts at 0 for every class).
-template <bool kFull, bool kFwd = false>
+template <bool kFull>
 __device__ __forceinline__ void index_word(uint64_t p0, uint64_t p1, uint64_t valid, uint32_t pos, uint32_t run[4],
                                            uint32_t inv) {
   uint64_t m[4];
@@ -495,36 +495,32 @@ __device__ __forceinline__ void index_word(uint64_t p0, uint64_t p1, uint64_t va
 #pragma unroll
   for (int c = 0; c < 4; ++c)
     slot[c] = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[c] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[c], run[c]));
-  uint32_t k = slot[3] | (kFwd ? 3u << 14 : 0u);
-  k = __builtin_amdgcn_inverse_ballot_w64(m[2]) ? slot[2] | (kFwd ? 2u << 14 : 0u) : k;
-  k = __builtin_amdgcn_inverse_ballot_w64(m[1]) ? slot[1] | (kFwd ? 1u << 14 : 0u) : k;
+  uint32_t k = slot[3];
+  k = __builtin_amdgcn_inverse_ballot_w64(m[2]) ? slot[2] : k;
+  k = __builtin_amdgcn_inverse_ballot_w64(m[1]) ? slot[1] : k;
   k = __builtin_amdgcn_inverse_ballot_w64(m[0]) ? slot[0] : k;
-  if constexpr (kFwd)
-    lds_store_u16(inv + 2u * pos, (uint16_t)(__builtin_amdgcn_inverse_ballot_w64(valid) ? k : 0u));
-  else if (kFull || __builtin_amdgcn_inverse_ballot_w64(valid))
-    lds_store_u16(inv + 2u * k, (uint16_t)pos);
+  if (kFull || __builtin_amdgcn_inverse_ballot_w64(valid)) lds_store_u16(inv + 2u * k, (uint16_t)pos);
 #pragma unroll
   for (int c = 0; c < 4; ++c) run[c] += (uint32_t)__popcll(m[c]);
 }
 
-template <bool kFwd = false>
 __device__ __forceinline__ void build_index(const WmapRegs& wr, const UnitInfo& u, int wb, int we, int R,
                                             const WinCounts& wc, uint32_t inv, uint32_t lane) {
   uint32_t run[4];
   run[0] = 0;
-  run[1] = kFwd ? 0u : wc.own[0];
-  run[2] = kFwd ? 0u : run[1] + wc.own[1];
-  run[3] = kFwd ? 0u : run[2] + wc.own[2];
+  run[1] = wc.own[0];
+  run[2] = run[1] + wc.own[1];
+  run[3] = run[2] + wc.own[2];
   const int full_end = u.rows == R ? max(wb, min(we, u.npos >> 6)) : wb;
   const uint32_t pos0 = lane - (uint32_t)wb * 64u;
   // words held in lanes w (planes a0/a1) and w - 64 (planes b0/b1)
   for (int w = wb; w < min(full_end, 64); ++w)
-    index_word<true, kFwd>(read_lane64(wr.a0, w), read_lane64(wr.a1, w), ~0ull, pos0 + 64u * w, run, inv);
+    index_word<true>(read_lane64(wr.a0, w), read_lane64(wr.a1, w), ~0ull, pos0 + 64u * w, run, inv);
   for (int w = max(wb, 64); w < full_end; ++w)
-    index_word<true, kFwd>(read_lane64(wr.b0, w - 64), read_lane64(wr.b1, w - 64), ~0ull, pos0 + 64u * w, run, inv);
+    index_word<true>(read_lane64(wr.b0, w - 64), read_lane64(wr.b1, w - 64), ~0ull, pos0 + 64u * w, run, inv);
   for (int w = full_end; w < we; ++w) {
     const bool hi = w >= 64;
-    index_word<false, kFwd>(read_lane64(hi ? wr.b0 : wr.a0, w & 63), read_lane64(hi ? wr.b1 : wr.a1, w & 63),
+    index_word<false>(read_lane64(hi ? wr.b0 : wr.a0, w & 63), read_lane64(hi ? wr.b1 : wr.a1, w & 63),
                       valid_mask(w, u.npos, R, u.rows), pos0 + 64u * w, run, inv);
   }
 }
