@@ -1813,8 +1813,14 @@ __device__ __forceinline__ void mm_uni_word(const MmUniWord<RB, UNI>& bk, int nb
 // offset and entry count), the
 // unit table is read beside the width map rather than after it, and the
 // argument block is read only once those loads are issued.
+//
+// UNI: the one width class, -1 for mixed widths, or kMmOneWord for mixed widths
+// and items of a single word, which have no next word to hold registers for (100
+// instead of 150 in 16-row tiles: two workgroups of eight waves on a CU, not one).
+constexpr int kMmOneWord = -2;
+
 template <int NW, int RB, int UNI = -1>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 16 ? 4 : 2))) void vbq_mm_kernel(
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(UNI == kMmOneWord ? 4 : 2))) void vbq_mm_kernel(
     const uint8_t* __restrict__ blob, uint32_t off_wmap, uint32_t tile_words, uint32_t chunk_words, uint32_t wmap_words,
     int32_t G, int32_t N, uint32_t geo, int32_t U, int32_t M, MmArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -1861,6 +1867,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 1
       // The words of one range, the next one in flight while one is multiplied.
       auto walk = [&](auto& A, auto& B, int f, int n, auto&& load, auto&& mul) __attribute__((always_inline)) {
         if (f >= n) return;
+        if constexpr (UNI == kMmOneWord) {
+          for (int w = f; w < n; w += step) {
+            load(A, w);
+            mul(A, w);
+          }
+          return;
+        }
         load(A, f);
         int w = f;
         for (; w + 2 * step < n; w += 2 * step) {
@@ -2328,6 +2341,9 @@ vbq_status launch_mm_uni(const MmArgs& a, int uni, int NW, int lds, hipStream_t 
     case 1: return launch_mm_rb<RB, 1>(a, NW, lds, s);
     case 2: return launch_mm_rb<RB, 2>(a, NW, lds, s);
     case 3: return launch_mm_rb<RB, 3>(a, NW, lds, s);
+    case kMmOneWord:
+      if constexpr (RB != 2) return launch_mm_rb<RB, kMmOneWord>(a, NW, lds, s);
+      return VBQ_ERR_UNSUPPORTED;  // (mm_class names it for no 32-row tile)
     default: return launch_mm_rb<RB, -1>(a, NW, lds, s);
   }
 }
@@ -2336,8 +2352,7 @@ vbq_status launch_mm_uni(const MmArgs& a, int uni, int NW, int lds, hipStream_t 
 // unit, LDS bytes.  Each wave walks its words one after the other, so small
 // matrices split their tiles over more waves, up to eight (sixteen waves of a
 // workgroup leave a wave 128 registers: 2048 x 2048 M = 4 took 8.1 us against
-// 4.3), as long as the whole grid fits the GPU at once (about 20 waves per CU
-// at this kernel's register use).
+// 4.3), as long as the grid has at most 20 waves per CU.
 bool mm_shape(const DevMatrix& m, int M, int* NWo, int* lgSo, int* ldso) {
   int NWt = kMinWaves;
   while (NWt < 8 && (int64_t)m.T * NWt * 2 <= 256 * 20) NWt *= 2;
@@ -2350,6 +2365,18 @@ bool mm_shape(const DevMatrix& m, int M, int* NWo, int* lgSo, int* ldso) {
   *lgSo = lgS;
   *ldso = NW * wbytes;
   return NW * wbytes <= kLdsLimit;
+}
+
+// The kernel's last template argument.  Items of one word take the variant that
+// holds no second one where the grid has more than 2048 waves, two a SIMD: 6144 x
+// 2048 M = 4 / 16 6.6 / 8.5 -> 5.8 / 7.9 us, 40000 x 256 M = 8 7.1 -> 6.6.
+// Smaller grids have the registers and are not faster for giving them up (2048 x
+// 2048 M = 4 / 16 4.0 / 4.9 against 4.1 / 5.1), nor are 32-row tiles (20000 x 512
+// M = 5 6.3 against 6.4).
+int mm_class(const DevMatrix& m, int NW, int lgS) {
+  const int uni = one_class(m);
+  const bool one_word = max_slice_cols(m.logR, m.C, lgS) * m.R <= 64;
+  return uni < 0 && one_word && (int64_t)m.T * NW > 2048 && m.R != 32 ? kMmOneWord : uni;
 }
 
 vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t ldx, int M, void* y, int64_t ldy,
@@ -2366,7 +2393,7 @@ vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
   a.lgS = lgS;
   a.yf16 = (flags & VBQ_Y_F16) ? 1 : 0;
   // row blocks of 16 per group: one, two or four (R = 16, 32, >= 64)
-  const int uni = one_class(m);
+  const int uni = mm_class(m, NW, lgS);
   if (m.R == 16) return launch_mm_uni<1>(a, uni, NW, lds, s);
   if (m.R == 32) return launch_mm_uni<2>(a, uni, NW, lds, s);
   return launch_mm_uni<4>(a, uni, NW, lds, s);
@@ -2439,8 +2466,8 @@ const char* kernel_name(const DevMatrix& m, uint32_t flags, int M) {
 #define VBQ_MM_NAMES(rb)                                                                                       \
   {{"vbq_mm_kernel<4," rb ",0>", "vbq_mm_kernel<8," rb ",0>"}, {"vbq_mm_kernel<4," rb ",1>", "vbq_mm_kernel<8," rb ",1>"}, \
    {"vbq_mm_kernel<4," rb ",2>", "vbq_mm_kernel<8," rb ",2>"}, {"vbq_mm_kernel<4," rb ",3>", "vbq_mm_kernel<8," rb ",3>"}, \
-   {"vbq_mm_kernel<4," rb ">", "vbq_mm_kernel<8," rb ">"}}
-  static const char* const kMm[3][5][2] = {VBQ_MM_NAMES("1"), VBQ_MM_NAMES("2"), VBQ_MM_NAMES("4")};
+   {"vbq_mm_kernel<4," rb ">", "vbq_mm_kernel<8," rb ">"}, {"vbq_mm_kernel<4," rb ",-2>", "vbq_mm_kernel<8," rb ",-2>"}}
+  static const char* const kMm[3][6][2] = {VBQ_MM_NAMES("1"), VBQ_MM_NAMES("2"), VBQ_MM_NAMES("4")};
 #undef VBQ_MM_NAMES
   if (M <= 0) return "none";
   const int uni = one_class(m), c = uni < 0 ? 4 : uni;
@@ -2456,7 +2483,8 @@ const char* kernel_name(const DevMatrix& m, uint32_t flags, int M) {
   }
   int NW, lgS, lds;
   if (!mm_shape(m, M, &NW, &lgS, &lds)) return "none";
-  return kMm[m.R == 16 ? 0 : m.R == 32 ? 1 : 2][c][NW == 4 ? 0 : 1];
+  const int mc = mm_class(m, NW, lgS);
+  return kMm[m.R == 16 ? 0 : m.R == 32 ? 1 : 2][mc == kMmOneWord ? 5 : c][NW == 4 ? 0 : 1];
 }
 
 // ---------------------------------------------------------------------------

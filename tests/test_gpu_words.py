@@ -50,8 +50,9 @@ def test_dequant_exact_and_unaligned(vbq, N, K, R, C, uniform):
     assert buf[0].item() == 7.0 and torch.all(buf[1 + N * K:] == 7.0)  # nothing written outside
 
 
-# the matrix-core product: also a grid beyond the wave-pair kernel's (two rows)
-MM_GEOMS = GEOMS[:6] + [(33000, 256, 16, 1)]
+# the matrix-core product: also a grid beyond the wave-pair kernel's (two rows),
+# and the variant for items of one word in grids of more than 2048 waves
+MM_GEOMS = GEOMS[:6] + [(33000, 256, 16, 1), (33000, 256, 64, 1)]
 
 
 @pytest.mark.parametrize("uniform", [0, 1, 2, 4, 8])
@@ -64,6 +65,8 @@ def test_batch_products_within_the_float32_bound(vbq, N, K, R, C, M, uniform):
     Wp, bits, q, s = _packed(vbq, N, K, R, C, uniform)
     if M > 2 or uniform or Wp.desc.n_units > 2048:
         assert vbq.kernel_name(Wp.desc, M).startswith("vbq_mm_kernel<")
+    if N == 33000 and not uniform:
+        assert vbq.kernel_name(Wp.desc, M).endswith(",-2>") or (M == 2 and Wp.desc.n_units <= 2048)
     X = synth.draw_x(synth.rng_for(311, M), M, K)
     X[0] = 0
     X[0, K - 1] = 1.0
