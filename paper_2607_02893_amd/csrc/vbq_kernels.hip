@@ -1816,7 +1816,7 @@ __device__ __forceinline__ void mm_uni_word(const MmUniWord<RB, UNI>& bk, int nb
 //
 // UNI: the one width class, -1 for mixed widths, or kMmOneWord for mixed widths
 // and items of a single word, which have no next word to hold registers for (100
-// instead of 150 in 16-row tiles: two workgroups of eight waves on a CU, not one).
+// instead of 150 in 16-row tiles, so five waves a SIMD instead of three).
 constexpr int kMmOneWord = -2;
 
 template <int NW, int RB, int UNI = -1>
@@ -2352,10 +2352,16 @@ vbq_status launch_mm_uni(const MmArgs& a, int uni, int NW, int lds, hipStream_t 
 // unit, LDS bytes.  Each wave walks its words one after the other, so small
 // matrices split their tiles over more waves, up to eight (sixteen waves of a
 // workgroup leave a wave 128 registers: 2048 x 2048 M = 4 took 8.1 us against
-// 4.3), as long as the grid has at most 20 waves per CU.
+// 4.3).  With mixed widths only while all workgroups are resident at once: at
+// 150 registers one of eight waves fits a CU, but three of four waves, so
+// beyond 256 tiles eight waves mean a second round (9000 x 2112 M = 3 12.1 us
+// against 7.8 with four, 6144 x 4096 M = 4 9.5 against 8.3, 40000 x 256 M = 8
+// 6.6 against 4.6).  One-width kernels hold 72-118 registers and take eight up
+// to 20 waves per CU (28672 x 4096 1-bit M = 8 13.6 us against 14.2).
 bool mm_shape(const DevMatrix& m, int M, int* NWo, int* lgSo, int* ldso) {
+  const int max_waves = 256 * (one_class(m) < 0 ? 8 : 20);
   int NWt = kMinWaves;
-  while (NWt < 8 && (int64_t)m.T * NWt * 2 <= 256 * 20) NWt *= 2;
+  while (NWt < 8 && (int64_t)m.T * NWt * 2 <= max_waves) NWt *= 2;
   int lgS = log2_up((NWt + m.U - 1) / m.U);
   while (max_slice_cols(m.logR, m.C, lgS) > kMmMaxCols) ++lgS;
   const int wbytes = mm_wave_bytes(m.R, M);
@@ -2368,11 +2374,11 @@ bool mm_shape(const DevMatrix& m, int M, int* NWo, int* lgSo, int* ldso) {
 }
 
 // The kernel's last template argument.  Items of one word take the variant that
-// holds no second one where the grid has more than 2048 waves, two a SIMD: 6144 x
-// 2048 M = 4 / 16 6.6 / 8.5 -> 5.8 / 7.9 us, 40000 x 256 M = 8 7.1 -> 6.6.
-// Smaller grids have the registers and are not faster for giving them up (2048 x
-// 2048 M = 4 / 16 4.0 / 4.9 against 4.1 / 5.1), nor are 32-row tiles (20000 x 512
-// M = 5 6.3 against 6.4).
+// holds no second one where the grid has more than 2048 waves, two a SIMD
+// (measured in workgroups of eight waves: 40000 x 256 M = 8 7.1 -> 6.6 us, 33000 x
+// 256 M = 2 6.6 -> 6.2).  Smaller grids have the registers and are not faster for
+// giving them up (2048 x 2048 M = 4 / 16 4.0 / 4.9 against 4.1 / 5.1), nor are
+// 32-row tiles (20000 x 512 M = 5 6.3 against 6.4).
 int mm_class(const DevMatrix& m, int NW, int lgS) {
   const int uni = one_class(m);
   const bool one_word = max_slice_cols(m.logR, m.C, lgS) * m.R <= 64;
