@@ -1612,7 +1612,8 @@ struct MmWord {
 };
 
 // X rows 0 .. M-1 (fp16, stride ldx) as a buffer resource (the bytes up to the
-// end of row M-1) and this lane's row l % 16 at the first of its 16 weights.
+// end of row M-1, which launch_mm keeps below 4 GiB) and this lane's row l % 16
+// at the first of its 16 weights.
 struct XRows {
   __amdgpu_buffer_rsrc_t rsrc;
   uint32_t row;
@@ -1633,7 +1634,7 @@ __device__ __forceinline__ void load_mm_x(Word& bk, const XRows& xr, int w, int 
     const int col = min(RB == 4 ? (w << 6) >> logR : w * NC + i, cols - 1);
     const int xo = 128 * (j0 + col);  // wave-uniform
     bk.a[i][0] = __builtin_amdgcn_raw_buffer_load_b128(xr.rsrc, (int)xr.row, xo, 0);
-    bk.a[i][1] = __builtin_amdgcn_raw_buffer_load_b128(xr.rsrc, (int)xr.row + 16, xo, 0);
+    bk.a[i][1] = __builtin_amdgcn_raw_buffer_load_b128(xr.rsrc, (int)(xr.row + 16u), xo, 0);
   }
 }
 
@@ -2391,18 +2392,25 @@ vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
   if (!mm_shape(m, M, &NW, &lgS, &lds)) return VBQ_ERR_UNSUPPORTED;
   MmArgs a;
   a.m = m;
-  a.x = (const uint16_t*)x;
-  a.y = y;
   a.ldx = ldx;
   a.ldy = ldy;
-  a.M = M;
   a.lgS = lgS;
   a.yf16 = (flags & VBQ_Y_F16) ? 1 : 0;
   // row blocks of 16 per group: one, two or four (R = 16, 32, >= 64)
   const int uni = mm_class(m, NW, lgS);
-  if (m.R == 16) return launch_mm_uni<1>(a, uni, NW, lds, s);
-  if (m.R == 32) return launch_mm_uni<2>(a, uni, NW, lds, s);
-  return launch_mm_uni<4>(a, uni, NW, lds, s);
+  // X is addressed with 32-bit byte offsets: rows that span 4 GiB or more go as
+  // many to a launch as stay below it (one row is at most 128 MiB)
+  const int fit = (int)std::min<int64_t>(M, 1 + (((int64_t)1 << 31) - 1 - m.K) / ldx);
+  for (int m0 = 0; m0 < M; m0 += fit) {
+    a.x = (const uint16_t*)x + m0 * ldx;
+    a.y = (uint8_t*)y + m0 * ldy * (a.yf16 ? 2 : 4);
+    a.M = std::min(fit, M - m0);
+    const vbq_status st = m.R == 16   ? launch_mm_uni<1>(a, uni, NW, lds, s)
+                          : m.R == 32 ? launch_mm_uni<2>(a, uni, NW, lds, s)
+                                      : launch_mm_uni<4>(a, uni, NW, lds, s);
+    if (st != VBQ_OK) return st;
+  }
+  return VBQ_OK;
 }
 
 // Two rows on the matrix cores: one-width matrices and grids beyond the wave-pair
@@ -2880,9 +2888,7 @@ vbq_status vbq_gemm_small(const vbq_desc* desc, const void* blob_dev, int64_t M,
   const int Mi = (int)M;
   const uint32_t f = desc->flags;
   if (Mi == 1) return launch_mv<1>(m, f, X_dev, ldx, 1, Y_dev, ldy, s);
-  // (the matrix-core kernel addresses X with 32-bit offsets)
-  if (Mi == 2 && !(takes_mm(m, f) && ldx + desc->K < (1ll << 30)))
-    return launch_mv<2>(m, f, X_dev, ldx, 2, Y_dev, ldy, s);
+  if (Mi == 2 && !takes_mm(m, f)) return launch_mv<2>(m, f, X_dev, ldx, 2, Y_dev, ldy, s);
   return launch_mm(m, f, X_dev, ldx, Mi, Y_dev, ldy, s);
 }
 
