@@ -2353,21 +2353,32 @@ vbq_status launch_mm_uni(const MmArgs& a, int uni, int NW, int lds, hipStream_t 
 // unit, LDS bytes.  Each wave walks its words one after the other, so small
 // matrices split their tiles over more waves, up to eight (sixteen waves of a
 // workgroup leave a wave 128 registers: 2048 x 2048 M = 4 took 8.1 us against
-// 4.3).  With mixed widths only while all workgroups are resident at once: at
-// 150 registers one of eight waves fits a CU, but three of four waves, so
-// beyond 256 tiles eight waves mean a second round (9000 x 2112 M = 3 12.1 us
-// against 7.8 with four, 6144 x 4096 M = 4 9.5 against 8.3, 40000 x 256 M = 8
-// 6.6 against 4.6).  One-width kernels hold 72-118 registers and take eight up
-// to 20 waves per CU (28672 x 4096 1-bit M = 8 13.6 us against 14.2).
+// 4.3), while all workgroups are resident at once.  Mixed widths:
+//   * 16-row tiles (150 registers: one workgroup of eight waves a CU, three of
+//     four): eight up to 256 tiles, four beyond, also where a tile has eight
+//     units (M = 3 / 16, us with eight and four: 6000 x 8256 16.6 / 24.6 and 15.4 /
+//     23.7, 12288 x 8256 24.4 / 36.3 and 20.4 / 34.0, 9000 x 2112 12.1 and 7.8);
+//   * taller ones (117-122 registers: two of eight): eight up to 512 tiles where a
+//     wave still gets eight words of its tile (28672 x 4096 17.2 / 19.1 and 18.3 /
+//     19.3, 16384 x 8256 19.6 / 26.4 and 22.8 / 26.9; with fewer words the longer
+//     sum over the waves costs as much: 28672 x 1024 7.2 / 7.9 and 7.2 / 7.7,
+//     16384 x 1024 5.3 / 6.3 and 5.3 / 5.9) or where three units would leave four
+//     waves uneven work (28672 x 576 6.0 / 6.4 and 6.8 / 7.3).
+// One-width kernels hold 72-118 registers and split for eight up to 20 waves per
+// CU (28672 x 4096 1-bit M = 8 13.6 us against 14.2), and eight units keep eight
+// waves beyond (10500 x 14336 1-bit M = 2 20.1 against 20.9).
 bool mm_shape(const DevMatrix& m, int M, int* NWo, int* lgSo, int* ldso) {
-  const int max_waves = 256 * (one_class(m) < 0 ? 8 : 20);
-  int NWt = kMinWaves;
-  while (NWt < 8 && (int64_t)m.T * NWt * 2 <= max_waves) NWt *= 2;
-  int lgS = log2_up((NWt + m.U - 1) / m.U);
+  const bool mixed = one_class(m) < 0;
+  const int eight_tiles = !mixed ? 640 : m.R > 16 && (m.tile_words >= 128 || m.U == 3) ? 512 : 256;
+  const int most = m.T <= eight_tiles ? 8 : kMinWaves;
+  int lgS = log2_up((most + m.U - 1) / m.U);
+  // no slices without a word (9000 x 576 M = 16 7.1 -> 5.9 us); two units are as
+  // fast or faster with theirs (16384 x 128 M = 4 3.4 against 3.6)
+  if (m.U != 2) lgS = std::min(lgS, log2_up(m.chunk_words));
   while (max_slice_cols(m.logR, m.C, lgS) > kMmMaxCols) ++lgS;
   const int wbytes = mm_wave_bytes(m.R, M);
   int NW = kMinWaves;  // (fewer waves than items is fine: items are dealt in turn)
-  while (NW < 8 && NW < (m.U << lgS) && 2 * NW * wbytes <= kLdsLimit) NW *= 2;
+  while (NW < (mixed ? most : 8) && NW < (m.U << lgS) && 2 * NW * wbytes <= kLdsLimit) NW *= 2;
   *NWo = NW;
   *lgSo = lgS;
   *ldso = NW * wbytes;

@@ -1,0 +1,40 @@
+"""Which launch the matrix-core product takes (vbq_kernel_name, descriptors only):
+waves per workgroup on both sides of each line of the rule, in the geometry
+that the packer chooses and in others."""
+
+import numpy as np
+import pytest
+
+from paper_2607_02893_amd import vbq
+
+
+def _desc(N, K, mixed=True, R=0, C=0):
+    bits = np.ones((N, K // 64), dtype=np.uint8)
+    if mixed:
+        bits[:, ::2] = 4
+        bits[0, 0] = 8
+    return vbq.pack_size(bits, K, R, C)[1]
+
+
+def _args(desc, M):
+    name = vbq.kernel_name(desc, M)
+    assert name.startswith("vbq_mm_kernel<"), name
+    return name[len("vbq_mm_kernel<"):-1].split(",")
+
+
+@pytest.mark.parametrize("M", [3, 4, 16])
+@pytest.mark.parametrize("N,K,waves", [
+    (4096, 8256, 8), (4097, 8256, 4), (6000, 8256, 4), (5120, 13824, 4), (12288, 8256, 4),  # eight units, 16-row tiles
+    (4096, 2048, 8), (4112, 2048, 4), (9000, 576, 4), (12288, 320, 4),                      # four units, three
+    (16384, 8256, 8), (20000, 8256, 4), (16384, 4096, 4), (16384, 576, 8), (20000, 576, 4),  # 32-row tiles
+    (28672, 4096, 8), (32768, 4096, 8), (32769, 4096, 4), (28672, 2048, 4), (28672, 576, 8),  # 64-row tiles
+])
+def test_waves_of_mixed_products(N, K, waves, M):
+    d = _desc(N, K)
+    assert d.tile_rows == (16 if N < 16353 else 32 if N < 28609 else 64)
+    assert int(_args(d, M)[0]) == waves
+
+
+@pytest.mark.parametrize("N,K,waves", [(10240, 2048, 8), (10256, 2048, 4), (10256, 14336, 8), (300, 64, 4)])
+def test_waves_of_one_width_products(N, K, waves):
+    assert int(_args(_desc(N, K, mixed=False), 4)[0]) == waves
