@@ -2342,9 +2342,10 @@ vbq_status launch_mm_uni(const MmArgs& a, int uni, int NW, int lds, hipStream_t 
     case 1: return launch_mm_rb<RB, 1>(a, NW, lds, s);
     case 2: return launch_mm_rb<RB, 2>(a, NW, lds, s);
     case 3: return launch_mm_rb<RB, 3>(a, NW, lds, s);
-    case kMmOneWord:
-      if constexpr (RB != 2) return launch_mm_rb<RB, kMmOneWord>(a, NW, lds, s);
-      return VBQ_ERR_UNSUPPORTED;  // (mm_class names it for no 32-row tile)
+    case kMmOneWord:  // (mm_class names it for no 32-row tile, and for 16-row tiles of four waves only)
+      if constexpr (RB == 1) return launch_mm_nw<4, RB, kMmOneWord>(a, lds, s);
+      if constexpr (RB == 4) return launch_mm_rb<RB, kMmOneWord>(a, NW, lds, s);
+      return VBQ_ERR_UNSUPPORTED;
     default: return launch_mm_rb<RB, -1>(a, NW, lds, s);
   }
 }
@@ -2386,15 +2387,19 @@ bool mm_shape(const DevMatrix& m, int M, int* NWo, int* lgSo, int* ldso) {
 }
 
 // The kernel's last template argument.  Items of one word take the variant that
-// holds no second one where the grid has more than 2048 waves, two a SIMD
-// (measured in workgroups of eight waves: 40000 x 256 M = 8 7.1 -> 6.6 us, 33000 x
-// 256 M = 2 6.6 -> 6.2).  Smaller grids have the registers and are not faster for
-// giving them up (2048 x 2048 M = 4 / 16 4.0 / 4.9 against 4.1 / 5.1), nor are
-// 32-row tiles (20000 x 512 M = 5 6.3 against 6.4).
-int mm_class(const DevMatrix& m, int NW, int lgS) {
+// holds no second one:
+//   * in 16-row tiles (100 registers instead of 150) beyond 768 tiles, which are
+//     what the other variant has resident at once, three workgroups of four waves
+//     a CU (M = 3 / 16, us without and with it: 14000 x 1024 6.0 / 8.2 and 5.4 / 7.8,
+//     16000 x 768 5.8 / 7.6 and 5.3 / 7.5); smaller grids are up to 4% slower with
+//     it (12288 x 1024 4.7 / 6.3 and 4.8 / 6.5, 6000 x 1024 4.0 / 5.1 and 4.1 / 5.2);
+//   * in tiles of 64 rows and more always (28672 x 256 4.1 / 4.6 and 3.8 / 4.3,
+//     65536 x 256 5.4 / 6.6 and 5.1 / 6.1);
+//   * in 32-row tiles not (20000 x 512 M = 5 6.3 and 6.4).
+int mm_class(const DevMatrix& m, int lgS) {
   const int uni = one_class(m);
   const bool one_word = max_slice_cols(m.logR, m.C, lgS) * m.R <= 64;
-  return uni < 0 && one_word && (int64_t)m.T * NW > 2048 && m.R != 32 ? kMmOneWord : uni;
+  return uni < 0 && one_word && (m.R == 16 ? m.T > 768 : m.R > 32) ? kMmOneWord : uni;
 }
 
 vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t ldx, int M, void* y, int64_t ldy,
@@ -2408,7 +2413,7 @@ vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
   a.lgS = lgS;
   a.yf16 = (flags & VBQ_Y_F16) ? 1 : 0;
   // row blocks of 16 per group: one, two or four (R = 16, 32, >= 64)
-  const int uni = mm_class(m, NW, lgS);
+  const int uni = mm_class(m, lgS);
   // X is addressed with 32-bit byte offsets: rows that span 4 GiB or more go as
   // many to a launch as stay below it (one row is at most 128 MiB)
   const int fit = (int)std::min<int64_t>(M, 1 + (((int64_t)1 << 31) - 1 - m.K) / ldx);
@@ -2508,7 +2513,7 @@ const char* kernel_name(const DevMatrix& m, uint32_t flags, int M) {
   }
   int NW, lgS, lds;
   if (!mm_shape(m, M, &NW, &lgS, &lds)) return "none";
-  const int mc = mm_class(m, NW, lgS);
+  const int mc = mm_class(m, lgS);
   return kMm[m.R == 16 ? 0 : m.R == 32 ? 1 : 2][mc == kMmOneWord ? 5 : c][NW == 4 ? 0 : 1];
 }
 

@@ -38,3 +38,15 @@ def test_waves_of_mixed_products(N, K, waves, M):
 @pytest.mark.parametrize("N,K,waves", [(10240, 2048, 8), (10256, 2048, 4), (10256, 14336, 8), (300, 64, 4)])
 def test_waves_of_one_width_products(N, K, waves):
     assert int(_args(_desc(N, K, mixed=False), 4)[0]) == waves
+
+
+@pytest.mark.parametrize("M", [3, 16])
+@pytest.mark.parametrize("N,K,R,C,one_word", [
+    (12288, 1024, 0, 0, False), (12289, 1024, 0, 0, True), (14000, 1088, 16, 5, False), (20000, 256, 0, 0, False),
+    (28672, 256, 0, 0, True), (28672, 320, 0, 0, True), (28672, 512, 0, 0, False), (300, 256, 64, 1, True),
+    (300, 256, 256, 1, False),
+])
+def test_one_word_variant(N, K, R, C, one_word, M):
+    args = _args(_desc(N, K, True, R, C), M)
+    assert (args[-1] == "-2") == one_word
+    assert args[-1] != "-2" or args[0] == "4" or int(args[1]) == 4
