@@ -1611,30 +1611,38 @@ struct MmWord {
   u32x4 a[kCols][2];
 };
 
-// X rows 0 .. M-1 (fp16, stride ldx) as a buffer resource (the bytes up to the
-// end of row M-1, which launch_mm keeps below 4 GiB) and this lane's row l % 16
-// at the first of its 16 weights.
+// X rows 0 .. M-1 (fp16, stride ldx): the bytes up to the end of row M-1, which
+// launch_mm keeps below 4 GiB, and this lane's row l % 16 at the first of its 16
+// weights.
 struct XRows {
-  __amdgpu_buffer_rsrc_t rsrc;
-  uint32_t row;
+  const uint16_t* x;
+  uint32_t bytes, row;
 };
 __device__ __forceinline__ XRows mm_x_rows(const uint16_t* x, int64_t ldx, int M, int K, uint32_t lane) {
-  return XRows{__builtin_amdgcn_make_buffer_rsrc((void*)x, 0, (int)(2 * ((int64_t)(M - 1) * ldx + K)), 0x00020000),
+  return XRows{x, (uint32_t)(2 * ((int64_t)(M - 1) * ldx + K)),
                2u * (uint32_t)((int64_t)min((int)(lane & 15u), M - 1) * ldx + 16 * (int)(lane >> 4))};
 }
 
 // The activations of word w's columns (X through a buffer resource covering
 // the M rows; lanes of rows past M - 1 read row M - 1, whose products are
-// never stored).  Columns past the unit's last one read the last one.
-template <int RB, typename Word>
+// never stored).  kRagged: the unit's columns may end inside the word; the loads
+// of the columns past its last one go through an empty resource, which fetches
+// nothing (their blocks are not multiplied).  With the last column read again for
+// them instead, 16000 x 256 2-bit M = 16 took 6.5 us against 4.5, 12288 x 256
+// mixed 5.9 against 4.5 and 16000 x 8256 2-bit 43.8 against 40.3; not issuing them
+// at all slowed the one-width kernels (12288 x 14336 1-bit M = 2 22.7 against 20.1).
+template <int RB, bool kRagged, typename Word>
 __device__ __forceinline__ void load_mm_x(Word& bk, const XRows& xr, int w, int logR, int j0, int cols) {
   constexpr int NC = Word::kCols;
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
-    const int col = min(RB == 4 ? (w << 6) >> logR : w * NC + i, cols - 1);
-    const int xo = 128 * (j0 + col);  // wave-uniform
-    bk.a[i][0] = __builtin_amdgcn_raw_buffer_load_b128(xr.rsrc, (int)xr.row, xo, 0);
-    bk.a[i][1] = __builtin_amdgcn_raw_buffer_load_b128(xr.rsrc, (int)(xr.row + 16u), xo, 0);
+    const int col = RB == 4 ? (w << 6) >> logR : w * NC + i;  // wave-uniform, as all but the row
+    const bool real = !kRagged || i == 0 || col < cols;
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc((void*)xr.x, 0, real ? (int)xr.bytes : 0, 0x00020000);
+    const int xo = real ? 128 * (j0 + col) : 0;
+    bk.a[i][0] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)xr.row, xo, 0);
+    bk.a[i][1] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(xr.row + 16u), xo, 0);
   }
 }
 
@@ -1718,7 +1726,7 @@ __device__ __forceinline__ void mm_word(const MmWord<RB>& bk, int nblocks, float
   broadcast_rows(bk.s, sb);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    if (RB == 4 || i < nblocks) {  // wave-uniform
+    if (i < nblocks) {  // wave-uniform
       float s = (float)__builtin_bit_cast(_Float16, (uint16_t)sb[i]);
       __asm__("" : "+v"(s));  // converted once (a mixed-precision FMA would convert it four times at half rate)
       const float4_t d = mm_products(bk.w[i], bk.c[i], bk.a[i / RB][0], bk.a[i / RB][1]);
@@ -1787,7 +1795,7 @@ __device__ __forceinline__ void mm_uni_word(const MmUniWord<RB, UNI>& bk, int nb
   broadcast_rows(bk.s, sb);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    if (RB == 4 || i < nblocks) {  // wave-uniform
+    if (i < nblocks) {  // wave-uniform
       float s = (float)__builtin_bit_cast(_Float16, (uint16_t)sb[i]);
       __asm__("" : "+v"(s));
       uint32_t q[8];
@@ -1820,7 +1828,7 @@ __device__ __forceinline__ void mm_uni_word(const MmUniWord<RB, UNI>& bk, int nb
 // instead of 150 in 16-row tiles, so five waves a SIMD instead of three).
 constexpr int kMmOneWord = -2;
 
-template <int NW, int RB, int UNI = -1>
+template <int NW, int RB, bool kRagged, int UNI = -1>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(UNI == kMmOneWord ? 4 : 2))) void vbq_mm_kernel(
     const uint8_t* __restrict__ blob, uint32_t off_wmap, uint32_t tile_words, uint32_t chunk_words, uint32_t wmap_words,
     int32_t G, int32_t N, uint32_t geo, int32_t U, int32_t M, MmArgs a) {
@@ -1891,7 +1899,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(UNI == 
           mul(A, w);
         }
       };
-      auto nblocks = [&](int w) __attribute__((always_inline)) { return RB == 4 ? 4 : min(4, (u.cols - w * (4 / RB)) * RB); };
+      // (the one-width kernels keep the test of each block where it is always true:
+      // without it as scheduled 2048 x 14336 8-bit M = 2 took 12.0 us against 10.0)
+      constexpr bool kTest = kRagged || (UNI >= 0 && RB != 4);
+      auto nblocks = [&](int w) __attribute__((always_inline)) { return kTest ? min(4, (u.cols - w * (4 / RB)) * RB) : 4; };
       if constexpr (UNI >= 0) {
         const XRows xr = mm_x_rows(a.x, a.ldx, M, mat.K, lane);
         const uint32_t first = (uint32_t)t * (uint32_t)(R * mat.G) + (uint32_t)u.j0 * (uint32_t)u.rows;
@@ -1899,7 +1910,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(UNI == 
         walk(A, B, wb + rg, we,
              [&](MmUniWord<RB, UNI>& b, int w) __attribute__((always_inline)) {
                load_mm_uni_word<RB, UNI>(b, mat, u, first, w, lane);
-               load_mm_x<RB>(b, xr, w, mat.logR, u.j0, u.cols);
+               load_mm_x<RB, kRagged>(b, xr, w, mat.logR, u.j0, u.cols);
              },
              [&](const MmUniWord<RB, UNI>& b, int w) __attribute__((always_inline)) {
                mm_uni_word<RB, UNI>(b, nblocks(w), h, acc);
@@ -1925,7 +1936,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(UNI == 
           MmWord<RB> A, B;
           walk(A, B, max(wb, w0) + rg, min(we, w0 + 64),
                [&](MmWord<RB>& b, int w) __attribute__((always_inline)) {
-                 load_mm_x<RB>(b, xr, w, mat.logR, u.j0, u.cols);
+                 load_mm_x<RB, kRagged>(b, xr, w, mat.logR, u.j0, u.cols);
                  load_mm_word<RB>(b, mat, word_entries(mat, u, sc, start, w0, w - w0), htab);
                },
                [&](const MmWord<RB>& b, int w) __attribute__((always_inline)) { mm_word<RB>(b, nblocks(w), acc); });
@@ -2306,9 +2317,9 @@ vbq_status launch_mv(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
 
 // Several rows on matrix cores: same item split as the one-row path (slices
 // of at most 32 columns, at least four items per tile).
-template <int NW, int RB, int UNI>
+template <int NW, int RB, bool kRagged, int UNI>
 vbq_status launch_mm_nw(const MmArgs& a, int lds, hipStream_t s) {
-  const void* kernel = (const void*)vbq_mm_kernel<NW, RB, UNI>;
+  const void* kernel = (const void*)vbq_mm_kernel<NW, RB, kRagged, UNI>;
   if (lds > 64 * 1024) {
     static std::atomic<uint64_t> done{0};
     vbq_status st = allow_big_lds(kernel, done);
@@ -2329,25 +2340,34 @@ vbq_status launch_mm_nw(const MmArgs& a, int lds, hipStream_t s) {
   return hip_status(hipLaunchKernel(kernel, dim3((unsigned)a.m.T), dim3(NW * 64), kargs, (size_t)lds, s));
 }
 
-template <int RB, int UNI>
+template <int RB, bool kRagged, int UNI>
 vbq_status launch_mm_rb(const MmArgs& a, int NW, int lds, hipStream_t s) {
-  if (NW == 4) return launch_mm_nw<4, RB, UNI>(a, lds, s);
-  return launch_mm_nw<8, RB, UNI>(a, lds, s);
+  if (NW == 4) return launch_mm_nw<4, RB, kRagged, UNI>(a, lds, s);
+  return launch_mm_nw<8, RB, kRagged, UNI>(a, lds, s);
 }
 
-template <int RB>
+template <int RB, bool kRagged>
 vbq_status launch_mm_uni(const MmArgs& a, int uni, int NW, int lds, hipStream_t s) {
   switch (uni) {
-    case 0: return launch_mm_rb<RB, 0>(a, NW, lds, s);
-    case 1: return launch_mm_rb<RB, 1>(a, NW, lds, s);
-    case 2: return launch_mm_rb<RB, 2>(a, NW, lds, s);
-    case 3: return launch_mm_rb<RB, 3>(a, NW, lds, s);
+    case 0: return launch_mm_rb<RB, kRagged, 0>(a, NW, lds, s);
+    case 1: return launch_mm_rb<RB, kRagged, 1>(a, NW, lds, s);
+    case 2: return launch_mm_rb<RB, kRagged, 2>(a, NW, lds, s);
+    case 3: return launch_mm_rb<RB, kRagged, 3>(a, NW, lds, s);
     case kMmOneWord:  // (mm_class names it for no 32-row tile, and for 16-row tiles of four waves only)
-      if constexpr (RB == 1) return launch_mm_nw<4, RB, kMmOneWord>(a, lds, s);
-      if constexpr (RB == 4) return launch_mm_rb<RB, kMmOneWord>(a, NW, lds, s);
+      if constexpr (RB == 1) return launch_mm_nw<4, RB, kRagged, kMmOneWord>(a, lds, s);
+      if constexpr (RB == 4) return launch_mm_rb<RB, kRagged, kMmOneWord>(a, NW, lds, s);
       return VBQ_ERR_UNSUPPORTED;
-    default: return launch_mm_rb<RB, -1>(a, NW, lds, s);
+    default: return launch_mm_rb<RB, kRagged, -1>(a, NW, lds, s);
   }
+}
+
+// Whether some unit's columns end inside a width-map word (16-row tiles: four
+// columns a word, 32-row tiles: two).  Where none does, the kernel without the
+// tests is the faster one (mixed widths, 16384 x 2048 M = 4 / 16 7.7 / 8.8 us with
+// them and 7.1 / 8.4 without; 4% over 245 shapes).
+bool mm_ragged(const DevMatrix& m) {
+  const int last = m.G - (m.U - 1) * m.C, in_word = cols_per_word(m.R) - 1;
+  return ((m.C | last) & in_word) != 0;
 }
 
 // Launch shape of the matrix-core kernel: waves per workgroup, slices per
@@ -2414,6 +2434,7 @@ vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
   a.yf16 = (flags & VBQ_Y_F16) ? 1 : 0;
   // row blocks of 16 per group: one, two or four (R = 16, 32, >= 64)
   const int uni = mm_class(m, lgS);
+  const bool ragged = mm_ragged(m);
   // X is addressed with 32-bit byte offsets: rows that span 4 GiB or more go as
   // many to a launch as stay below it (one row is at most 128 MiB)
   const int fit = (int)std::min<int64_t>(M, 1 + (((int64_t)1 << 31) - 1 - m.K) / ldx);
@@ -2421,9 +2442,11 @@ vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
     a.x = (const uint16_t*)x + m0 * ldx;
     a.y = (uint8_t*)y + m0 * ldy * (a.yf16 ? 2 : 4);
     a.M = std::min(fit, M - m0);
-    const vbq_status st = m.R == 16   ? launch_mm_uni<1>(a, uni, NW, lds, s)
-                          : m.R == 32 ? launch_mm_uni<2>(a, uni, NW, lds, s)
-                                      : launch_mm_uni<4>(a, uni, NW, lds, s);
+    const vbq_status st = m.R > 32    ? launch_mm_uni<4, false>(a, uni, NW, lds, s)
+                          : m.R == 16 ? (ragged ? launch_mm_uni<1, true>(a, uni, NW, lds, s)
+                                                : launch_mm_uni<1, false>(a, uni, NW, lds, s))
+                          : ragged    ? launch_mm_uni<2, true>(a, uni, NW, lds, s)
+                                      : launch_mm_uni<2, false>(a, uni, NW, lds, s);
     if (st != VBQ_OK) return st;
   }
   return VBQ_OK;
@@ -2493,11 +2516,15 @@ const char* kernel_name(const DevMatrix& m, uint32_t flags, int M) {
                                         {"vbq_mv_kernel<1,4,2>", "vbq_mv_kernel<1,8,2>", "vbq_mv_kernel<1,16,2>"},
                                         {"vbq_mv_kernel<1,4,3>", "vbq_mv_kernel<1,8,3>", "vbq_mv_kernel<1,16,3>"},
                                         {"vbq_mv_kernel<1,4>", "vbq_mv_kernel<1,8>", "vbq_mv_kernel<1,16>"}};
-#define VBQ_MM_NAMES(rb)                                                                                       \
-  {{"vbq_mm_kernel<4," rb ",0>", "vbq_mm_kernel<8," rb ",0>"}, {"vbq_mm_kernel<4," rb ",1>", "vbq_mm_kernel<8," rb ",1>"}, \
-   {"vbq_mm_kernel<4," rb ",2>", "vbq_mm_kernel<8," rb ",2>"}, {"vbq_mm_kernel<4," rb ",3>", "vbq_mm_kernel<8," rb ",3>"}, \
-   {"vbq_mm_kernel<4," rb ">", "vbq_mm_kernel<8," rb ">"}, {"vbq_mm_kernel<4," rb ",-2>", "vbq_mm_kernel<8," rb ",-2>"}}
-  static const char* const kMm[3][6][2] = {VBQ_MM_NAMES("1"), VBQ_MM_NAMES("2"), VBQ_MM_NAMES("4")};
+#define VBQ_MM_NAMES(rb, rag)                                                      \
+  {{"vbq_mm_kernel<4," rb "," rag ",0>", "vbq_mm_kernel<8," rb "," rag ",0>"},     \
+   {"vbq_mm_kernel<4," rb "," rag ",1>", "vbq_mm_kernel<8," rb "," rag ",1>"},     \
+   {"vbq_mm_kernel<4," rb "," rag ",2>", "vbq_mm_kernel<8," rb "," rag ",2>"},     \
+   {"vbq_mm_kernel<4," rb "," rag ",3>", "vbq_mm_kernel<8," rb "," rag ",3>"},     \
+   {"vbq_mm_kernel<4," rb "," rag ">", "vbq_mm_kernel<8," rb "," rag ">"},         \
+   {"vbq_mm_kernel<4," rb "," rag ",-2>", "vbq_mm_kernel<8," rb "," rag ",-2>"}}
+  static const char* const kMm[5][6][2] = {VBQ_MM_NAMES("1", "false"), VBQ_MM_NAMES("1", "true"), VBQ_MM_NAMES("2", "false"),
+                                           VBQ_MM_NAMES("2", "true"), VBQ_MM_NAMES("4", "false")};
 #undef VBQ_MM_NAMES
   if (M <= 0) return "none";
   const int uni = one_class(m), c = uni < 0 ? 4 : uni;
@@ -2514,7 +2541,7 @@ const char* kernel_name(const DevMatrix& m, uint32_t flags, int M) {
   int NW, lgS, lds;
   if (!mm_shape(m, M, &NW, &lgS, &lds)) return "none";
   const int mc = mm_class(m, lgS);
-  return kMm[m.R == 16 ? 0 : m.R == 32 ? 1 : 2][mc == kMmOneWord ? 5 : c][NW == 4 ? 0 : 1];
+  return kMm[m.R > 32 ? 4 : (m.R == 32 ? 2 : 0) + mm_ragged(m)][mc == kMmOneWord ? 5 : c][NW == 4 ? 0 : 1];
 }
 
 // ---------------------------------------------------------------------------

@@ -50,3 +50,14 @@ def test_one_word_variant(N, K, R, C, one_word, M):
     args = _args(_desc(N, K, True, R, C), M)
     assert (args[-1] == "-2") == one_word
     assert args[-1] != "-2" or args[0] == "4" or int(args[1]) == 4
+
+
+@pytest.mark.parametrize("uniform", [False, True])
+@pytest.mark.parametrize("N,K,R,C,ragged", [
+    (300, 1024, 0, 0, False), (300, 256, 0, 0, True), (300, 320, 0, 0, True), (300, 64, 0, 0, True), (300, 2048, 0, 0, False),
+    (300, 576, 16, 4, True), (300, 8256, 16, 128, True), (20000, 512, 0, 0, False), (20000, 256, 0, 0, True),
+    (20000, 576, 32, 2, True), (28672, 64, 0, 0, False), (300, 64, 256, 1, False),
+])
+def test_ragged_variant(N, K, R, C, ragged, uniform):
+    args = _args(_desc(N, K, not uniform, R, C), 4)
+    assert args[2] == ("true" if ragged else "false")
