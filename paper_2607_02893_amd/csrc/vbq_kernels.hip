@@ -1975,19 +1975,22 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(UNI == 
 // words), so each lane expands the four weights 4t .. 4t + 3 of an entry from
 // one dword of codes and the wave stores four whole groups per instruction,
 // 16 bytes a lane.  For 16-row tiles a word is 16 rows of four columns and the
-// four groups of a store are consecutive in memory.
+// four groups of a store are consecutive in memory.  A tile's slices are dealt
+// to 2^lgY workgroups of four waves, neighbours in the grid (they write the same
+// rows: 6000 x 2048 10.5 us against 11.1 with the tiles as neighbours).
 constexpr int kDequantWaves = 4;
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // W may be only 4-byte aligned
 
-__global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatrix mat, float* W, int lgS) {
+__global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatrix mat, float* W, int lgS, int lgY) {
   __shared__ __attribute__((aligned(16))) uint32_t hand_s[kDequantWaves * 128];  // per position: codes and class, scale
   const uint32_t lane = lane_id();
   const int wave = wave_id();
-  const int t = blockIdx.x;
+  const int t = (int)(blockIdx.x >> lgY);
+  const int first = (int)(blockIdx.x & ((1u << lgY) - 1u)) * kDequantWaves + wave;
   const uint32_t hand = (uint32_t)(size_t)(__attribute__((address_space(3))) uint32_t*)hand_s + 512u * (uint32_t)wave;
   const uint32_t grp = lane >> 4, sub = lane & 15u;
   const uint32_t mine = hand + 128u * grp;
-  for (int item = wave; item < (mat.U << lgS); item += kDequantWaves) {
+  for (int item = first; item < (mat.U << lgS); item += kDequantWaves << lgY) {
     const int k = item >> lgS, sl = item & ((1 << lgS) - 1);
     const UnitInfo u = load_unit(mat, t, k);
     const int per = (u.W + (1 << lgS) - 1) >> lgS;
@@ -2949,15 +2952,20 @@ vbq_status vbq_dequant(const vbq_desc* desc, const void* blob_dev, float* W_dev,
   vbq_status st = make_dev_matrix(desc, blob_dev, &m);
   if (st != VBQ_OK) return st;
   if ((uintptr_t)W_dev % 4) return VBQ_ERR_BUFFER;
-  // slices of a unit's words: enough waves for eight per SIMD (the rate comes
-  // from the stores and loads in flight), a word at least each
+  // a slice of a unit's words to each wave: slices of two words and more until
+  // there are 4096 waves, four a SIMD (10007 x 3136: 30.0 us with 2504 waves, 26.7
+  // with 5008), single words only below 2048 (4096 x 4096 13.2 us with 2048 waves of
+  // two words, 14.5 with 4096 of one; 28672 x 1024 26.1 and 30.8).  With all slices
+  // of a tile in one workgroup 256 x 14336, sixteen tiles, took 44.9 us against 5.4.
   const int64_t units = (int64_t)m.T * m.U;
   const int unit_words = (int)(((int64_t)m.C * m.R + 63) / 64);
-  int lgS = std::min(log2_up(std::max<int64_t>((8192 + units - 1) / units, (kDequantWaves + m.U - 1) / m.U)),
-                     log2_up(unit_words));
-  void* args[] = {&m, &W_dev, &lgS};
-  return hip_status(hipLaunchKernel((const void*)vbq_dequant_kernel, dim3((unsigned)m.T), dim3(kDequantWaves * 64), args, 0,
-                                    (hipStream_t)stream));
+  int lgS = 0;
+  for (int per = unit_words; per > 1 && (units << lgS) < (per > 2 ? 4096 : 2048); per = (per + 1) / 2) ++lgS;
+  int lgY = log2_up((((int64_t)m.U << lgS) + kDequantWaves - 1) / kDequantWaves);
+  while (((int64_t)m.T << lgY) > (1 << 30)) --lgY;  // (a workgroup takes several rounds of slices then)
+  void* args[] = {&m, &W_dev, &lgS, &lgY};
+  return hip_status(hipLaunchKernel((const void*)vbq_dequant_kernel, dim3((unsigned)m.T << lgY), dim3(kDequantWaves * 64),
+                                    args, 0, (hipStream_t)stream));
 }
 
 vbq_status vbq_step_plan_bytes(int32_t n, size_t* bytes) {
