@@ -176,7 +176,9 @@ vbq_status vbq_pack_size(int64_t N, int64_t K, const uint8_t* bits,
  * W: host float32[N][K] row-major; bits: host uint8[N][K/64].
  * blob: host buffer of blob_bytes >= vbq_pack_size() bytes, 8-byte aligned.
  * On success fills *desc.  Errors: NULL, SHAPE, BITS, NONFINITE (NaN/Inf in
- * W), SCALE_RANGE (a scale that overflows fp16), BUFFER, UNSUPPORTED. */
+ * W), SCALE_RANGE (a scale that overflows fp16), BUFFER, UNSUPPORTED.  Of
+ * several refused groups the first in entry order (tile by tile, down each
+ * column) is reported; with several threads, that of some tile that has one. */
 vbq_status vbq_pack(int64_t N, int64_t K, const float* W, const uint8_t* bits,
                     const vbq_pack_opts* opts, void* blob, size_t blob_bytes,
                     vbq_desc* desc);

@@ -413,6 +413,38 @@ struct Source {
   const uint16_t* scales = nullptr;  // vbq_pack_codes
 };
 
+// Quantize or encode group (r, j): its record, and its fp16 scale (a quantized
+// 1-bit group's when the queue is flushed).
+inline vbq_status pack_group(const Geometry& g, const Source& src, int64_t r, int64_t j, int b, uint8_t* dst,
+                             uint16_t* scale, MeanQueue* mq) {
+  if (src.W) return quantize_group(src.W + r * g.K + j * kGroup, b, dst, scale, mq);
+  const vbq_status st = record_of_levels(src.q + r * g.K + j * kGroup, b, dst);
+  if (st != VBQ_OK) return st;
+  const uint16_t sb = src.scales[r * g.G + j];
+  if (!fp16_finite(sb)) return VBQ_ERR_NONFINITE;
+  if (sb & 0x8000u) return VBQ_ERR_SCALE_RANGE;
+  *scale = sb;
+  return VBQ_OK;
+}
+
+// The status of tile t's first refused group in the order of the entries (down
+// each column), which is the one reported; the packing itself goes by rows and
+// knows a 1-bit mean only later.
+__attribute__((cold)) vbq_status first_refused(const Geometry& g, const Source& src, const uint8_t* bits, int64_t t) {
+  uint8_t record[8 * 8];
+  uint16_t scale;
+  MeanQueue mq;
+  for (int64_t j = 0; j < g.G; ++j) {
+    for (int64_t rl = 0; rl < g.tile_rows(t); ++rl) {
+      const int64_t r = t * g.R + rl;
+      vbq_status st = pack_group(g, src, r, j, bits[r * g.G + j], record, &scale, &mq);
+      if (st == VBQ_OK) st = flush_means(&mq);
+      if (st != VBQ_OK) return st;
+    }
+  }
+  return VBQ_OK;
+}
+
 vbq_status pack_impl(int64_t N, int64_t K, const Source& src, const uint8_t* bits,
                      const vbq_pack_opts* opts, void* blob, size_t blob_bytes, vbq_desc* desc) {
   if (!bits || !blob || !desc) return VBQ_ERR_NULL;
@@ -486,27 +518,15 @@ vbq_status pack_impl(int64_t N, int64_t K, const Source& src, const uint8_t* bit
           const int b = bits[r * g.G + j];
           const int c = class_of_bits((uint8_t)b);
           const uint32_t e = entry[(size_t)(rl * cols + jl)];
-          uint8_t* dst = codes[c] + (size_t)e * (8u << c);
-          vbq_status gs;
-          if (src.W) {
-            gs = quantize_group(src.W + r * g.K + j * kGroup, b, dst, &scales[c][e], &mq);
-          } else {
-            gs = record_of_levels(src.q + r * g.K + j * kGroup, b, dst);
-            const uint16_t sb = src.scales[r * g.G + j];
-            if (gs == VBQ_OK && !fp16_finite(sb)) gs = VBQ_ERR_NONFINITE;
-            if (gs == VBQ_OK && (sb & 0x8000u)) gs = VBQ_ERR_SCALE_RANGE;
-            scales[c][e] = sb;
-          }
-          if (gs != VBQ_OK) {
-            record_error(err, gs);
+          if (pack_group(g, src, r, j, b, codes[c] + (size_t)e * (8u << c), &scales[c][e], &mq) != VBQ_OK) {
+            record_error(err, first_refused(g, src, bits, t));
             return;
           }
         }
       }
       std::memcpy(wmap + units[(size_t)unit * kUnitRowWords + 4], planes.data(), planes.size() * 8);
     }
-    const vbq_status gs = flush_means(&mq);
-    if (gs != VBQ_OK) record_error(err, gs);
+    if (flush_means(&mq) != VBQ_OK) record_error(err, first_refused(g, src, bits, t));
   });
   if (err.load() != VBQ_OK) return (vbq_status)err.load();
   *desc = d;
