@@ -21,7 +21,9 @@
 #include <thread>
 #include <vector>
 
-#if defined(__x86_64__)
+// (VBQ_PACK_PORTABLE: without the AVX2 code, for tests)
+#if defined(__x86_64__) && !defined(VBQ_PACK_PORTABLE)
+#define VBQ_PACK_AVX2
 #include <immintrin.h>
 #endif
 
@@ -259,7 +261,7 @@ inline void sum_magnitudes(const float* const* w, int n, double* sum) {
   }
 }
 
-#if defined(__x86_64__)
+#if defined(VBQ_PACK_AVX2)
 #define VBQ_AVX2 __attribute__((target("avx2")))
 VBQ_AVX2 uint64_t sign_bits_avx2(const float* w) {
   uint64_t m = 0;
