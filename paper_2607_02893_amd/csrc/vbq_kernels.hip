@@ -1496,12 +1496,12 @@ __device__ __forceinline__ WordScan scan_words(const DevMatrix& mat, const UnitI
 
 // The entry at each lane's position of word w0 + l of a scan: byte offset of
 // its codes with the class in the low three bits (code sections and entries
-// are 8-byte aligned), byte offset of its scale, and whether the position is
-// real.  start: the class runs' entries at word w0.  Entries are clamped into
-// their section (a malformed blob can make the map and the unit table disagree).
+// are 8-byte aligned) and byte offset of its scale.  A padding position gets an
+// entry of class 0.  start: the class runs' entries at word w0.  Entries are
+// clamped into their section (a malformed blob can make the map and the unit
+// table disagree).
 struct LaneEntry {
   uint32_t codes, scale;
-  bool real;
 };
 
 __device__ __forceinline__ LaneEntry word_entries(const DevMatrix& mat, const UnitInfo& u, const WordScan& sc,
@@ -1530,12 +1530,11 @@ __device__ __forceinline__ LaneEntry word_entries(const DevMatrix& mat, const Un
     e.codes = __builtin_amdgcn_inverse_ballot_w64(m[c]) ? codes[c] : e.codes;
     e.scale = __builtin_amdgcn_inverse_ballot_w64(m[c]) ? scale[c] : e.scale;
   }
-  e.real = __builtin_amdgcn_inverse_ballot_w64(valid);
   return e;
 }
 
 // ---------------------------------------------------------------------------
-// Several activation rows (M <= 16): matrix cores.
+// Two to sixteen activation rows: matrix cores.
 //
 // Y[m][n] = sum_k w_hat[n][k] X[m][k] as 16 x 16 x 32 fp16 MFMA products
 // D[m][r] = sum_k X[m][k] q_r[k] over the 16 entries r of one group column
@@ -1543,13 +1542,14 @@ __device__ __forceinline__ LaneEntry word_entries(const DevMatrix& mat, const Un
 //   * lane l works for weight row r = l % 16 and group positions 16h .. 16h + 15,
 //     h = l / 16 (the k order inside a product is free as long as A and B agree);
 //   * A: activations X[l % 16][64 col + 16h ..] (two 16-byte loads);
-//   * B: the levels q of row r's entry, made exactly in fp16: a code field ORed
-//     into the mantissa of 1024.0 reads as 1024 + u, and one packed fp16 add
-//     gives q.  Each lane decodes its own entry's width with per-lane field
-//     positions, masks and offsets, so every lane runs the same code;
+//   * B: the levels of row r's entry as q 2^-10, made exactly in fp16: a masked
+//     code field is the subnormal u 2^-24, and one packed fp16 FMA gives q 2^-10
+//     (mm_products).  Each lane decodes its own entry's width with constants
+//     that it reads from the wave's LDS, so every lane runs the same code;
 //   * D: lane l holds D[4h + j][l % 16], j = 0..3, so each lane adds s * D for
 //     its weight row and four activation rows to registers over the slice's
-//     columns, in column order (results are bitwise repeatable).
+//     columns, in column order (results are bitwise repeatable), and the sums
+//     are multiplied by 2^10 when they are stored.
 // A wave takes a width-map word at a time, 64 positions = four blocks: 16 rows
 // of four columns (R = 16), 32 of two, or 64 rows of one.  Each lane looks up
 // one position's entry in registers and the four rows of 16 lanes are then
@@ -1562,11 +1562,11 @@ __device__ __forceinline__ LaneEntry word_entries(const DevMatrix& mat, const Un
 // 16-row tiles the reads of X, 2 KB a column for every tile.  Measured against
 // the earlier kernel (position map in LDS, then one block's lookup, loads and
 // products at a time), us a launch from a graph: 50304 x 2048 mixed M = 4 / 16
-// 29.3 / 43.5 -> 17.9 / 20.0, 16384 x 2048 M = 16 15.2 -> 9.4, 2048 x 8192
-// M = 16 13.2 -> 11.4, 2048 x 2048 M = 4 6.7 -> 4.2; one width, 28672 x 4096
-// 1-bit M = 8 30.3 -> 13.6, 2048 x 8192 2-bit M = 8 10.0 -> 8.5.  Two words
-// ahead were slower (25.0 at M = 16 on the 50304-row matrix) and no word ahead
-// with more waves equal at best (21.0).
+// 29.2 / 43.7 -> 17.0 / 19.2, 16384 x 2048 M = 16 15.1 -> 8.6, 2048 x 8192
+// M = 16 13.4 -> 11.2, 2048 x 2048 M = 4 6.8 -> 4.0; one width, 28672 x 4096
+// 1-bit M = 8 30.2 -> 12.8, 2048 x 8192 2-bit M = 8 10.2 -> 8.4.  Two words
+// ahead were slower (25.0 at M = 16 on the 50304-row matrix, against 20.0 then)
+// and no word ahead with more waves equal at best (21.0).
 // ---------------------------------------------------------------------------
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
@@ -2458,10 +2458,14 @@ vbq_status launch_mm(const DevMatrix& m, uint32_t flags, const void* x, int64_t 
 // Two rows on the matrix cores: one-width matrices and grids beyond the wave-pair
 // kernel's (without the flag that asks for the one-wave kernel).  The two-row
 // dot-product kernel reads x from LDS for every group of each row: 12301 x 2112
-// mixed 16.4 us against 9.8 here, 50304 x 2048 mixed 24.6 against 17.5, 2048 x
-// 8192 2-bit 9.4 against 6.7, 512 x 512 2-bit 5.0 against 2.7.  Smaller mixed
+// mixed 16.4 us against 9.5 here, 50304 x 2048 mixed 24.5 against 16.8, 2048 x
+// 8192 2-bit 9.6 against 6.8, 512 x 512 2-bit 5.1 against 2.5.  Smaller mixed
 // grids stay with the wave-pair kernel (or, with more than four units a tile,
-// the one-wave one), whose results the one-wave flag reproduces bit for bit.
+// the one-wave one) not for speed but because their results are then bit for bit
+// those under the one-wave flag: the matrix cores are as fast or faster there (us,
+// pair or one-wave kernel and matrix cores: 512 x 512 4.9 and 3.2, 2048 x 2048 4.9
+// and 4.0, 6000 x 2048 8.3 and 5.1, 28672 x 4096 20.2 and 17.2, 2048 x 8192 7.5 and
+// 7.7, eight units 4096 x 14336 17.1 and 11.4).
 bool takes_mm(const DevMatrix& m, uint32_t flags) {
   return !(flags & VBQ_ONE_WAVE_PER_UNIT) && (one_class(m) >= 0 || (int64_t)m.T * m.U > kPairMaxUnits);
 }
