@@ -1978,9 +1978,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(UNI == 
 // four groups of a store are consecutive in memory.  A tile's slices are dealt
 // to 2^lgY workgroups of four waves, neighbours in the grid (they write the same
 // rows: 6000 x 2048 10.5 us against 11.1 with the tiles as neighbours).
+// kOneColumn: 16-row tiles in units of one column, so a word has 16 real positions;
+// its four groups of lanes share them, four each.
 constexpr int kDequantWaves = 4;
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // W may be only 4-byte aligned
 
+template <bool kOneColumn>
 __global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatrix mat, float* W, int lgS, int lgY) {
   __shared__ __attribute__((aligned(16))) uint32_t hand_s[kDequantWaves * 128];  // per position: codes and class, scale
   const uint32_t lane = lane_id();
@@ -1989,7 +1992,8 @@ __global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatr
   const int first = (int)(blockIdx.x & ((1u << lgY) - 1u)) * kDequantWaves + wave;
   const uint32_t hand = (uint32_t)(size_t)(__attribute__((address_space(3))) uint32_t*)hand_s + 512u * (uint32_t)wave;
   const uint32_t grp = lane >> 4, sub = lane & 15u;
-  const uint32_t mine = hand + 128u * grp;
+  constexpr int kTurns = kOneColumn ? 4 : 16, kRows = kOneColumn ? 4 : 1;  // rows from one turn to the next
+  const uint32_t mine = hand + (kOneColumn ? 8u : 128u) * grp;
   for (int item = first; item < (mat.U << lgS); item += kDequantWaves << lgY) {
     const int k = item >> lgS, sl = item & ((1 << lgS) - 1);
     const UnitInfo u = load_unit(mat, t, k);
@@ -2006,15 +2010,16 @@ __global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatr
         const LaneEntry e = word_entries(mat, u, sc, start, w0, w - w0);
         lds_store_u32(hand + 8u * lane, e.codes);
         const uint32_t sbits = ld<uint16_t>(mat.blob, e.scale);
-        // the 16 positions of this lane's group: consecutive rows of one column
-        const int p0 = w * 64 + 16 * (int)grp;
+        // This lane's group of 16 lanes takes 16 positions in a row, which are
+        // consecutive rows of one column (kOneColumn: every fourth row).
+        const int p0 = w * 64 + (kOneColumn ? 1 : 16) * (int)grp;
         const int row0 = p0 & (mat.R - 1), col = p0 >> mat.logR;
-        const int n = col < u.cols ? min(16, u.rows - row0) : 0;
+        const int n = col < u.cols ? u.rows - row0 : 0;
         lds_phase();
-        uint32_t code[16];
+        uint32_t code[kTurns];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const uint32_t a = lds_u32(mine + 8u * (uint32_t)i);
+        for (int i = 0; i < kTurns; ++i) {
+          const uint32_t a = lds_u32(mine + 8u * (uint32_t)(kRows * i));
           // weights 4 sub .. + 3 are pairs 2 sub, 2 sub + 1: one dword at every width
           code[i] = ld<uint32_t>(mat.blob, (a & ~7u) + (((sub << (a & 3u)) >> 3) << 2));
           __builtin_amdgcn_sched_barrier(0x7F0);  // address arithmetic stays with its load (register use)
@@ -2024,8 +2029,8 @@ __global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatr
         lds_phase();
         float* dst = W + ((size_t)t * mat.R + row0) * mat.K + (size_t)(u.j0 + col) * 64 + 4u * sub;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const u32x2 h = *(const __attribute__((address_space(3))) u32x2*)(size_t)(mine + 8u * (uint32_t)i);
+        for (int i = 0; i < kTurns; ++i) {
+          const u32x2 h = *(const __attribute__((address_space(3))) u32x2*)(size_t)(mine + 8u * (uint32_t)(kRows * i));
           const uint32_t c = h.x & 3u, B = 1u << c, mask = (1u << B) - 1u;
           const float s = __uint_as_float(h.y);
           const uint32_t v = code[i] >> (((2u * sub) << c) & 15u);  // the pairs' bit offset in each half-word
@@ -2035,8 +2040,8 @@ __global__ __launch_bounds__(kDequantWaves * 64) void vbq_dequant_kernel(DevMatr
           o.y = s * __builtin_fmaf((float)((v >> 16) & mask), mul, off);
           o.z = s * __builtin_fmaf((float)((v >> B) & mask), mul, off);
           o.w = s * __builtin_fmaf((float)((v >> (16u + B)) & mask), mul, off);
-          if (i < n) __builtin_nontemporal_store(o, (f32x4_a4*)dst);
-          dst += mat.K;
+          if (kRows * i < n) __builtin_nontemporal_store(o, (f32x4_a4*)dst);
+          dst += (size_t)kRows * mat.K;
           __builtin_amdgcn_sched_barrier(0);
         }
         lds_phase();
@@ -2965,11 +2970,18 @@ vbq_status vbq_dequant(const vbq_desc* desc, const void* blob_dev, float* W_dev,
   const int unit_words = (int)(((int64_t)m.C * m.R + 63) / 64);
   int lgS = 0;
   for (int per = unit_words; per > 1 && (units << lgS) < (per > 2 ? 4096 : 2048); per = (per + 1) / 2) ++lgS;
+  // (a grid of at most half the units, or of the tiles)
   int lgY = log2_up((((int64_t)m.U << lgS) + kDequantWaves - 1) / kDequantWaves);
-  while (((int64_t)m.T << lgY) > (1 << 30)) --lgY;  // (a workgroup takes several rounds of slices then)
+  // One-column units are what the packer makes up to K = 256.  With their words
+  // expanded like full ones, a quarter of whose positions is real, 300 x 64 took
+  // 4.5 us against 2.9, 256 x 256 5.2 against 3.0 and 16000 x 256 9.4 against 6.2.
+  // (Looking for such words at the ends of wider units gained nothing: 2000 x 1088
+  // in units of 17 columns 6.0 and 6.0, 500 x 320, of two and a last one, 4.6 and 4.7.)
+  const bool one_column = m.R == 16 && m.C == 1;
+  const void* kernel = one_column ? (const void*)vbq_dequant_kernel<true> : (const void*)vbq_dequant_kernel<false>;
   void* args[] = {&m, &W_dev, &lgS, &lgY};
-  return hip_status(hipLaunchKernel((const void*)vbq_dequant_kernel, dim3((unsigned)m.T << lgY), dim3(kDequantWaves * 64),
-                                    args, 0, (hipStream_t)stream));
+  return hip_status(hipLaunchKernel(kernel, dim3((unsigned)m.T << lgY), dim3(kDequantWaves * 64), args, 0,
+                                    (hipStream_t)stream));
 }
 
 vbq_status vbq_step_plan_bytes(int32_t n, size_t* bytes) {

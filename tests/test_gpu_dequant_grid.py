@@ -1,6 +1,7 @@
 """vbq_dequant's split of the tiles over workgroups: unit counts that do not fill the
 last workgroup, units cut into slices of several words, one word and less, and
-grids large enough for whole units."""
+grids large enough for whole units; and the variant for one-column units of 16
+rows, with a last tile of fewer rows."""
 
 import numpy as np
 import pytest
@@ -22,9 +23,11 @@ def vbq():
 
 
 # N, K, tile rows, chunk groups: three units; five, and seven of one column; one
-# unit of 128 words; two of 32 words; 1200 tiles of five (whole units); 4100 tiles of one
+# unit of 128 words; two of 32 words; 1200 tiles of five (whole units); 4100 tiles of
+# one; one column of 1, 5 and 14 rows in the last tile; one-column units of 32 rows
 @pytest.mark.parametrize("N,K,R,C", [(100, 576, 0, 0), (70, 1280, 64, 4), (40, 448, 16, 1), (300, 2048, 256, 32),
-                                     (30, 16384, 16, 128), (19200, 320, 16, 1), (65590, 64, 16, 1)])
+                                     (30, 16384, 16, 128), (19200, 320, 16, 1), (65590, 64, 16, 1),
+                                     (17, 256, 0, 0), (5, 64, 0, 0), (30, 128, 0, 0), (45, 192, 32, 1)])
 def test_dequant_over_the_grid(vbq, N, K, R, C):
     print(f"dequant grid N={N} K={K} R={R} C={C}", flush=True)
     bits, q, s = synth.make_matrix(synth.MatrixSpec("t", N % 11, K % 7, N, K), 353)
