@@ -1557,8 +1557,8 @@ __device__ __forceinline__ LaneEntry word_entries(const DevMatrix& mat, const Un
 // through LDS and the loads of a whole word go out together, one word ahead of
 // the products.
 //
-// What bounds it: instruction issue (large matrices: about 330 instructions a
-// word, 240 of them VALU), two dependent memory trips (small ones), and for
+// What bounds it: instruction issue (large matrices: about 310 instructions a
+// word, 250 of them VALU), two dependent memory trips (small ones), and for
 // 16-row tiles the reads of X, 2 KB a column for every tile.  Measured against
 // the earlier kernel (position map in LDS, then one block's lookup, loads and
 // products at a time), us a launch from a graph: 50304 x 2048 mixed M = 4 / 16
