@@ -51,7 +51,7 @@ def test_dequant_exact_and_unaligned(vbq, N, K, R, C, uniform):
 
 
 # the matrix-core product: also a grid beyond the wave-pair kernel's (two rows),
-# and the variant for items of one word in grids of more than 2048 waves
+# and the variant for items of one word (16-row tiles beyond 768 of them, 64-row tiles)
 MM_GEOMS = GEOMS[:6] + [(33000, 256, 16, 1), (33000, 256, 64, 1)]
 
 
